@@ -13,9 +13,9 @@
 //                     matched slot of each flagged sector is recorded
 //                     (carve_scan_kernel.h; k_frag_scan in
 //                     carve_fragment_kernel.h for fragments)
-//   k_reduce / k_scan_blocks / k_apply<EmitIds>   popcount prefix ->
-//                     ascending flagged ids (per image, image order)
-//   k_image_offsets   (batches) where each image's ids start
+//   k_reduce, k_emit_ids   chunk sums of the hit words, then ascending flagged
+//                     ids (per image, image order) and, for batches, where
+//                     each image's ids start; k_emit_ids alone up to 512 MiB
 // Confirmation (Section 3.1), from the slot each flagged unit matched:
 //   k_confirm_count   byte comparison with every compatible candidate
 //   prefix sum        output offsets (counts read on the device)
@@ -138,16 +138,18 @@ struct TauMergeItems {
 // so a grid sized for a count read on the device need not cover its upper
 // bound. Chunks past the count are not touched (their sums are not scanned).
 // Within a chunk, consecutive threads take consecutive items (the sum does not
-// depend on the order), so every load instruction is coalesced.
-template <class Items>
+// depend on the order), so every load instruction is coalesced. kItems: items
+// per thread, for chunks of another size than kItemsPerBlock.
+template <class Items, int kItems = kItemsPerThread>
 __global__ __launch_bounds__(kBlockThreads) void k_reduce(Items items, Count count, uint64_t* __restrict__ blk_sums) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
+  constexpr uint64_t kChunk = (uint64_t)kBlockThreads * kItems;
   const uint64_t n = count.get();
-  for (uint64_t c = blockIdx.x; c * kItemsPerBlock < n; c += gridDim.x) {
-    const uint64_t base = c * kItemsPerBlock + threadIdx.x;
+  for (uint64_t c = blockIdx.x; c * kChunk < n; c += gridDim.x) {
+    const uint64_t base = c * kChunk + threadIdx.x;
     uint64_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
+    for (int k = 0; k < kItems; ++k) {
       const uint64_t i = base + (uint64_t)k * kBlockThreads;
       if (i < n) s += items(i);
     }
@@ -157,20 +159,19 @@ __global__ __launch_bounds__(kBlockThreads) void k_reduce(Items items, Count cou
   }
 }
 
-// One block: exclusive offsets of the block sums; total into *total. Only
-// the blocks that hold items are scanned (a count read on the device can be
-// far below the capacity the launches were sized for). A scan's compaction
-// also clears its confirmation marker (*clear, see kConfirmedWord). Each
-// thread takes a run of kScanRun consecutive sums per pass, its loads issued
+// One block: exclusive offsets of the block sums (chunks of `chunk` items);
+// total into *total. Only the blocks that hold items are scanned (a count read
+// on the device can be far below the capacity the launches were sized for).
+// Each thread takes a run of kScanRun consecutive sums per pass, its loads issued
 // together, so a pass of 4096 sums costs one memory round trip (a pass of 256,
 // one sum per thread, made the 8192 sums of a 2 GiB fragment image 23 us).
 constexpr int kScanRun = 16;
 __global__ __launch_bounds__(kBlockThreads) void k_scan_blocks(const uint64_t* __restrict__ blk_sums, Count items,
                                                               uint64_t* __restrict__ blk_off,
                                                               uint64_t* __restrict__ total,
-                                                              uint64_t* __restrict__ clear = nullptr) {
+                                                              uint64_t chunk = kItemsPerBlock) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
-  const uint64_t n_blk = (items.get() + kItemsPerBlock - 1) / kItemsPerBlock;
+  const uint64_t n_blk = (items.get() + chunk - 1) / chunk;
   uint64_t carry = 0;
   for (uint64_t b0 = 0; b0 < n_blk; b0 += (uint64_t)kBlockThreads * kScanRun) {
     const uint64_t first = b0 + (uint64_t)threadIdx.x * kScanRun;
@@ -189,42 +190,125 @@ __global__ __launch_bounds__(kBlockThreads) void k_scan_blocks(const uint64_t* _
     }
     carry += t;
   }
-  if (threadIdx.x == 0) {
-    *total = carry;
-    if (clear) *clear = 0;
-  }
+  if (threadIdx.x == 0) *total = carry;
 }
 
-// Hit words -> ascending ids of the flagged sectors, relative to their image
-// (and, for batches, the image of each); ids at positions cap and beyond are
-// not written (the count is still complete). An Emit type gives k_apply an item's
-// raw value (load), its count (count_of; 0 for the value 0) and what to write
-// for it at its exclusive position (emit); finish(n, end) runs once per scan
-// of n items, with end = the total.
-template <class Src>
-struct EmitIds {
-  static constexpr bool kDenseOut = false;   // a variable number of records per item
-  Src src;
-  const uint64_t* words;
+// Hit words -> ascending ids of the flagged units, relative to their image
+// (and, for batches, the image of each id, and the position of each image's
+// first id). Ids at positions cap and beyond are not written (the count is
+// still complete). Block c takes the words [c 256 kItems, (c + 1) 256 kItems)
+// and finds how many ids come before them by itself, so neither a scan of the
+// chunk sums nor (kDirect) the sums themselves need a launch:
+// * kDirect: it counts the bits of every word before its own;
+// * else it adds up the sums (k_reduce) of the chunks before its own, or, with
+//   many chunks, reads its offset (k_scan_blocks).
+// The launches are what this part of a step costs: each takes about 4 us on
+// the device, where its data would take well under 1. Against reduce, scan and
+// emit (and for batches a kernel for the images' positions): a 64 KiB buffer
+// without allocation 18.9 -> 12.3 us, a 64 MiB disk's whole step 79 -> 66 us,
+// an 8 GiB disk's 1389 -> 1382 us.
+struct IdsOut {
   uint64_t* ids;
-  uint32_t* img_of;   // null for one image
-  uint64_t cap;       // room in ids (and img_of)
-  __device__ __forceinline__ uint64_t load(uint64_t i) const { return words[i]; }
-  __device__ __forceinline__ uint64_t count_of(uint64_t x) const { return (uint64_t)__popcll(x); }
-  __device__ __forceinline__ void emit(uint64_t i, uint64_t x, uint64_t pos) const {
-    if (!x || pos >= cap) return;
-    const uint32_t im = src.image_of_tile(i);
-    const uint64_t first = (i - src.image(im).tile_begin) * kTileSectors;
-    while (x && pos < cap) {
-      const int b = __ffsll((long long)x) - 1;
-      ids[pos] = first + (uint64_t)b;
-      if (img_of) img_of[pos] = im;
-      ++pos;
-      x &= x - 1;
+  uint32_t* img_of;    // null for one image
+  uint64_t* img_off;   // batches: n_images + 1 positions
+  uint64_t cap;        // room in ids (and img_of)
+  uint64_t* total;     // receives the count
+  uint64_t* clear;     // the confirmation marker to clear, or null (see kConfirmedWord)
+};
+template <class Src, int kItems, bool kDirect>
+__global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint64_t* __restrict__ words, uint64_t n,
+                                                            const uint64_t* __restrict__ before, uint32_t scanned,
+                                                            IdsOut out) {
+  constexpr uint32_t kChunk = kBlockThreads * kItems;
+  constexpr uint32_t kWaves = kBlockThreads / kWave;
+  __shared__ uint64_t wave_before[kWaves];
+  __shared__ uint32_t wave_own[kWaves];
+  __shared__ uint32_t word_pos[Src::kManyImages ? kChunk : 1];   // ids of the chunk before each of its words
+  const uint32_t t = threadIdx.x, l = t % kWave, w = t / kWave;
+  const uint64_t c = blockIdx.x, c0 = c * kChunk, i0 = c0 + (uint64_t)t * kItems;
+  uint64_t x[kItems];
+  if (i0 + kItems <= n) {
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) x[k] = words[i0 + k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) x[k] = i0 + k < n ? words[i0 + k] : 0;
+  }
+  uint64_t b = 0;
+  if constexpr (kDirect) {
+#pragma unroll 4
+    for (uint64_t i = 2 * t; i < c0; i += 2 * kBlockThreads) {   // c0 is even
+      const u64x2 v = *(const u64x2*)(words + i);
+      b += (uint64_t)(__popcll(v.x) + __popcll(v.y));
+    }
+  } else if (scanned) {
+    if (t == 0) b = before[c];
+  } else {
+#pragma unroll 4
+    for (uint64_t i = t; i < c; i += kBlockThreads) b += before[i];
+  }
+  uint32_t own = 0;
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) own += (uint32_t)__popcll(x[k]);
+  uint32_t incl = own;
+#pragma unroll
+  for (int o = 1; o < (int)kWave; o <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)incl, o);
+    if (l >= (uint32_t)o) incl += y;
+    b += shfl_u64(b, l ^ (uint32_t)o);
+  }
+  if (l == kWave - 1) {
+    wave_own[w] = incl;
+    wave_before[w] = b;
+  }
+  __syncthreads();
+  uint64_t base = 0;
+  uint32_t pos_in = incl - own, all = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kWaves; ++i) {
+    base += wave_before[i];
+    pos_in += i < w ? wave_own[i] : 0u;
+    all += wave_own[i];
+  }
+  const bool last = c == gridDim.x - 1;
+  if (last && t == 0) {
+    *out.total = base + all;
+    if (out.clear) *out.clear = 0;
+  }
+  // the images the chunk's words belong to (uniform searches)
+  uint32_t im0 = 0, im1 = 0;
+  if constexpr (Src::kManyImages) {
+    im0 = src.image_of_tile(c0);
+    im1 = src.image_of_tile((c0 + kChunk < n ? c0 + kChunk : n) - 1);
+  }
+  uint64_t pos = base + pos_in;
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    if constexpr (Src::kManyImages) word_pos[t * kItems + k] = (uint32_t)(pos - base);
+    uint64_t v = x[k], p = pos;
+    pos += (uint64_t)__popcll(v);
+    if (v && p < out.cap) {
+      const uint32_t im = src.image_between(i0 + k, im0, im1);
+      const uint64_t first = (i0 + k - src.image(im).tile_begin) * kTileSectors;
+      do {
+        out.ids[p] = first + (uint64_t)(__ffsll((long long)v) - 1);
+        if (out.img_of) out.img_of[p] = im;
+        ++p;
+        v &= v - 1;
+      } while (v && p < out.cap);
     }
   }
-  __device__ __forceinline__ void finish(uint64_t, uint64_t) const {}
-};
+  if constexpr (Src::kManyImages) {
+    __syncthreads();
+    // images that start in this chunk; in the last block, also the empty ones at the end and the total
+    for (uint64_t i = (uint64_t)src.first_from(c0) + t; i <= src.n; i += kBlockThreads) {
+      const uint64_t at = src.d[i].tile_begin;
+      if (at < n && at >= c0 + kChunk) break;
+      if (at < n) out.img_off[i] = base + word_pos[at - c0];
+      else if (last) out.img_off[i] = base + all;
+    }
+  }
+}
 // u32 counts -> exclusive offsets (out[n] = total).
 template <class T>
 struct EmitOffsets {
@@ -244,7 +328,10 @@ struct EmitOffsets {
 __device__ __forceinline__ uint32_t stage_index(uint32_t j) { return j + (j >> 5); }
 constexpr uint32_t kStageWords = kItemsPerBlock + kItemsPerBlock / 32;
 
-// Chunks as in k_reduce.
+// Items' exclusive offsets (chunks as in k_reduce). An Emit type gives an item's
+// raw value (load), its count (count_of; 0 for the value 0) and what to write
+// for it at its exclusive position (emit); finish(n, end) runs once, with end =
+// the total.
 template <class Emit>
 __global__ __launch_bounds__(kBlockThreads) void k_apply(Emit e, Count count, const uint64_t* __restrict__ blk_off) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
@@ -302,28 +389,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_apply(Emit e, Count count, co
       }
     }
   }
-}
-
-// Batches: first flagged-id position of each image (img_off[n] = total), from
-// the block offsets of the compaction and the words of the image's block that
-// precede its first tile. One wave per image: its lanes popcount those words
-// (at most kItemsPerBlock - 1) in strides of the wave, then add up.
-__global__ void k_image_offsets(ManyImages src, const uint64_t* __restrict__ words,
-                                const uint64_t* __restrict__ blk_off, const uint64_t* __restrict__ total,
-                                uint64_t* __restrict__ img_off) {
-  const uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;   // uniform in the wave
-  const uint32_t lane = threadIdx.x % kWave;
-  if (i > src.n) return;
-  const uint64_t w = src.d[i].tile_begin;
-  if (w >= src.d[src.n].tile_begin) {
-    if (lane == 0) img_off[i] = *total;
-    return;
-  }
-  const uint64_t b = w / kItemsPerBlock;
-  uint32_t c = 0;
-  for (uint64_t k = b * kItemsPerBlock + lane; k < w; k += kWave) c += (uint32_t)__popcll(words[k]);
-  for (int o = kWave / 2; o; o >>= 1) c += (uint32_t)__shfl_xor((int)c, o);
-  if (lane == 0) img_off[i] = blk_off[b] + c;
 }
 
 // Batches, for callers that cannot wait: totals, per-image offsets, ids and
@@ -1169,7 +1234,39 @@ int validate_image(const void* image, uint64_t n_bytes, uint32_t tau0, uint32_t 
   return CARVE_OK;
 }
 
-// Launch the scan kernel, the compaction and (batches) the per-image offsets.
+// The compaction of n > 0 hit words into ids. ws: room for a sum and an offset
+// per chunk of kItemsPerBlock words. items counts a word's bits (and, after a
+// position-split scan, makes the word: must_reduce). One launch up to
+// kDirectWords (512 MiB of sectors): the last block then reads 128 KiB of
+// words, about a microsecond more than its own. Past that the chunk sums first,
+// and in k_emit_ids up to kSummedChunks of them per block; chunks of 1024 words
+// keep enough blocks to fill the chip, larger scans take chunks of 4096.
+constexpr uint64_t kDirectWords = 16384;
+constexpr uint64_t kSummedChunks = 4096;
+template <class Src, class Items>
+void launch_ids(const Src& src, const uint64_t* words, uint64_t n, uint64_t* ws, const IdsOut& out, hipStream_t s,
+                const Items& items, bool must_reduce) {
+  if (n <= kDirectWords && !must_reduce) {
+    k_emit_ids<Src, 1, true><<<cdiv(n, kBlockThreads), kBlockThreads, 0, s>>>(src, words, n, nullptr, 0, out);
+    return;
+  }
+  const Count count{n, nullptr};
+  uint64_t nb = cdiv(n, kItemsPerBlock);
+  if (nb <= kSummedChunks) {
+    k_reduce<Items><<<nb, kBlockThreads, 0, s>>>(items, count, ws);
+    k_emit_ids<Src, kItemsPerThread, false><<<nb, kBlockThreads, 0, s>>>(src, words, n, ws, 0, out);
+    return;
+  }
+  constexpr int kWide = 16;
+  nb = cdiv(n, (uint64_t)kBlockThreads * kWide);
+  k_reduce<Items, kWide><<<nb, kBlockThreads, 0, s>>>(items, count, ws);
+  const bool scanned = nb > kSummedChunks;
+  if (scanned)
+    k_scan_blocks<<<1, kBlockThreads, 0, s>>>(ws, count, ws + nb, out.total, (uint64_t)kBlockThreads * kWide);
+  k_emit_ids<Src, kWide, false><<<nb, kBlockThreads, 0, s>>>(src, words, n, scanned ? ws + nb : ws, scanned, out);
+}
+
+// Launch the scan kernel and the compaction.
 template <class Src>
 int launch_scan(carve_scan* sc, const Src& src) {
   const carve_index* idx = sc->idx;
@@ -1223,26 +1320,19 @@ int launch_scan(carve_scan* sc, const Src& src) {
     sc->timed = true;
   }
   HIP_TRY(hipEventRecord(sc->kernel_done, s));
-  const uint64_t nb = cdiv(n_words, kItemsPerBlock);
-  uint64_t* sums = sc->ws.as<uint64_t>();
-  uint64_t* offs = sums + nb;
+  const IdsOut out{sc->ids.as<uint64_t>(),
+                   sc->batch ? sc->img_of.as<uint32_t>() : nullptr,
+                   sc->batch ? sc->img_off.as<uint64_t>() : nullptr,
+                   ~0ull,
+                   d_count,
+                   d_count + kConfirmedWord};
   if (split)   // the position-split scan's words, merged into the bitmap while counting
-    k_reduce<<<nb, kBlockThreads, 0, s>>>(
-        TauMergeItems{sc->tau_words.as<uint64_t>(), cdiv(n_words, kPositions), sc->bitmap.as<uint64_t>(), n_words,
-                      one.tau0, (uint32_t)(one.n_sectors % kTileSectors)},
-        Count{n_words, nullptr}, sums);
+    launch_ids(src, sc->bitmap.as<uint64_t>(), n_words, sc->ws.as<uint64_t>(), out, s,
+               TauMergeItems{sc->tau_words.as<uint64_t>(), cdiv(n_words, kPositions), sc->bitmap.as<uint64_t>(),
+                             n_words, one.tau0, (uint32_t)(one.n_sectors % kTileSectors)}, true);
   else
-    k_reduce<<<nb, kBlockThreads, 0, s>>>(PopcountItems{sc->bitmap.as<uint64_t>()}, Count{n_words, nullptr}, sums);
-  k_scan_blocks<<<1, kBlockThreads, 0, s>>>(sums, Count{n_words, nullptr}, offs, d_count, d_count + kConfirmedWord);
-  k_apply<<<nb, kBlockThreads, 0, s>>>(
-      EmitIds<Src>{src, sc->bitmap.as<uint64_t>(), sc->ids.as<uint64_t>(), sc->batch ? sc->img_of.as<uint32_t>() : nullptr,
-                   ~0ull},
-      Count{n_words, nullptr}, offs);
-  if constexpr (std::is_same<Src, ManyImages>::value) {
-    const uint64_t per_block = kBlockThreads / kWave;
-    k_image_offsets<<<cdiv(sc->n_images + 1, per_block), kBlockThreads, 0, s>>>(
-        src, sc->bitmap.as<uint64_t>(), offs, d_count, sc->img_off.as<uint64_t>());
-  }
+    launch_ids(src, sc->bitmap.as<uint64_t>(), n_words, sc->ws.as<uint64_t>(), out, s,
+               PopcountItems{sc->bitmap.as<uint64_t>()}, false);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }
@@ -1910,25 +2000,22 @@ extern "C" int scan_image_noalloc(const carve_index* idx, const void* image, uin
   uint64_t* bitmap = sw;
   uint64_t* tau_words = sw + kNoAllocMaxWords;
   uint64_t* sums = sw + 2 * kNoAllocMaxWords;
-  uint64_t* offs = sums + kNoAllocMaxChunks;
+  uint64_t* ctr = sums + 2 * kNoAllocMaxChunks;
   const OneImage src{ImageDesc{(const uint8_t*)image, n_sectors, 0, tau0, tau_mode == CARVE_TAU_ANY ? 1u : 0u}};
   const uint32_t per_cu = idx->cfg.blocks_per_cu;
   const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
-  const uint64_t nb = cdiv(n_words, kItemsPerBlock);
+  const IdsOut out{ids, nullptr, nullptr, cap, count, nullptr};
   if (use_split(idx, src.d.any_tau)) {   // as scan_image: the position-split scan
     CARVE_TRY(launch_k_scan_tau(idx->sig_kind, idx->layout, src.d, cdiv(n_words, kPositions), chunk, per_cu,
-                                idx->view(), idx->weights, tau_words, nullptr, offs + kNoAllocMaxChunks, s));
-    k_reduce<<<nb, kBlockThreads, 0, s>>>(TauMergeItems{tau_words, cdiv(n_words, kPositions), bitmap, n_words,
-                                                        tau0, (uint32_t)(n_sectors % kTileSectors)},
-                                          Count{n_words, nullptr}, sums);
+                                idx->view(), idx->weights, tau_words, nullptr, ctr, s));
+    launch_ids(src, bitmap, n_words, sums, out, s,
+               TauMergeItems{tau_words, cdiv(n_words, kPositions), bitmap, n_words, tau0,
+                             (uint32_t)(n_sectors % kTileSectors)}, true);
   } else {
     CARVE_TRY(launch_k_scan<kFlagBits>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(), idx->weights, bitmap,
                                         nullptr, s, idx->layout));
-    k_reduce<<<nb, kBlockThreads, 0, s>>>(PopcountItems{bitmap}, Count{n_words, nullptr}, sums);
+    launch_ids(src, bitmap, n_words, sums, out, s, PopcountItems{bitmap}, false);
   }
-  k_scan_blocks<<<1, kBlockThreads, 0, s>>>(sums, Count{n_words, nullptr}, offs, count);
-  k_apply<<<nb, kBlockThreads, 0, s>>>(EmitIds<OneImage>{src, bitmap, ids, nullptr, cap}, Count{n_words, nullptr},
-                                       offs);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }

@@ -149,11 +149,11 @@ __device__ __forceinline__ uint64_t fragment_signature(const uint32_t* w) {
 // unit j is bytes [4j, 4j + 64); d.n_sectors holds the number of windows.
 struct FragmentWindows {
   static constexpr uint32_t kUnitBytes = kFragBytes, kUnitStride = kWindowStride;
-  static constexpr bool kAnyPosition = true;
+  static constexpr bool kAnyPosition = true, kManyImages = false;
   ImageDesc d;
   __device__ __forceinline__ uint64_t n_tiles() const { return (d.n_sectors + kTileSectors - 1) / kTileSectors; }
   __device__ __forceinline__ const ImageDesc& image(uint32_t) const { return d; }
-  __device__ __forceinline__ uint32_t image_of_tile(uint64_t) const { return 0; }
+  __device__ __forceinline__ uint32_t image_between(uint64_t, uint32_t, uint32_t) const { return 0; }
 };
 
 // find_slot reading each bucket as two 64-byte halves in turn. k_insert

@@ -47,19 +47,20 @@ __device__ __forceinline__ TileRef tile_of(const ImageDesc& d, uint64_t g, uint3
 struct OneImage {
   static constexpr uint32_t kUnitBytes = kSectorBytes, kUnitStride = kSectorBytes;
   static constexpr bool kAnyPosition = false;   // the image's own rule applies
+  static constexpr bool kManyImages = false;
   ImageDesc d;
   __device__ __forceinline__ uint64_t n_tiles() const { return (d.n_sectors + kTileSectors - 1) / kTileSectors; }
   // `cursor` is the image of the previous lookup (tiles are visited in increasing order)
   __device__ __forceinline__ TileRef tile(uint64_t g, uint32_t&) const { return tile_of(d, g, 0); }
   __device__ __forceinline__ const ImageDesc& image(uint32_t) const { return d; }
-  __device__ __forceinline__ uint32_t image_of_tile(uint64_t) const { return 0; }
+  __device__ __forceinline__ uint32_t image_between(uint64_t, uint32_t, uint32_t) const { return 0; }
 };
 
 // A batch: descriptors in device memory, n + 1 of them (the last one only
 // carries the total tile count in tile_begin).
 struct ManyImages {
   static constexpr uint32_t kUnitBytes = kSectorBytes, kUnitStride = kSectorBytes;
-  static constexpr bool kAnyPosition = false;
+  static constexpr bool kAnyPosition = false, kManyImages = true;
   const ImageDesc* __restrict__ d;
   uint32_t n;
   __device__ __forceinline__ uint64_t n_tiles() const { return d[n].tile_begin; }
@@ -81,11 +82,21 @@ struct ManyImages {
     return tile_of(d[cursor], g, cursor);
   }
   __device__ __forceinline__ const ImageDesc& image(uint32_t i) const { return d[i]; }
-  __device__ __forceinline__ uint32_t image_of_tile(uint64_t g) const {   // last i with d[i].tile_begin <= g
-    uint32_t lo = 0, hi = n - 1;
+  // The last image i of [lo, hi] with d[i].tile_begin <= g (tile g is in one of them).
+  __device__ __forceinline__ uint32_t image_between(uint64_t g, uint32_t lo, uint32_t hi) const {
     while (lo < hi) {
       const uint32_t mid = (lo + hi + 1) >> 1;
       if (d[mid].tile_begin <= g) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+  }
+  __device__ __forceinline__ uint32_t image_of_tile(uint64_t g) const { return image_between(g, 0, n - 1); }
+  // The first i of [0, n] with d[i].tile_begin >= g.
+  __device__ __forceinline__ uint32_t first_from(uint64_t g) const {
+    uint32_t lo = 0, hi = n;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (d[mid].tile_begin >= g) hi = mid; else lo = mid + 1;
     }
     return lo;
   }

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+from gpu_util import assert_same_matches, gpu_flags_and_matches, oracle_flags_and_matches
 from paper_0901_1307_amd import carve
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +96,44 @@ def test_batch_images_at_chunk_edges(words):
     r = carve.batch_confirm_matches(idx, b)
     got = np.stack([r["image"], r["disk_sector"], r["sector_in_file"]], 1).astype(np.int64)
     assert np.array_equal(got, np.concatenate(recs))
+
+
+# lengths of a signature's candidate list on both sides of the mask's short form (32) and of its ranks (63)
+@pytest.mark.parametrize("length", [1, 31, 32, 33, 62, 63, 64, 70])
+@pytest.mark.parametrize("any_tau", [False, True])
+def test_candidate_list_lengths(length, any_tau):
+    rng = np.random.default_rng(length)
+    a = rng.integers(40, 200, SECTOR, dtype=np.uint8)
+    b = a.copy()
+    b[100] += 1   # the same djb2: 33 * 1 less 33
+    b[101] -= 33
+    masters = np.where(np.arange(length)[:, None] % 3 == 1, b, a).astype(np.uint8)
+    offsets = [0, length // 2, length]
+    image = rng.integers(0, 256, (200, SECTOR), dtype=np.uint8)
+    image[::5], image[1::7] = a, b
+    idx = carve.build_master_index(torch.from_numpy(masters).reshape(-1).cuda(), offsets)
+    flags, matches, _ = gpu_flags_and_matches(idx, torch.from_numpy(image).reshape(-1).cuda(), 3, any_tau)
+    want_flags, want = oracle_flags_and_matches(masters, offsets, image.reshape(-1), 3, any_tau)
+    assert np.array_equal(flags, want_flags)
+    assert_same_matches(matches, want)
+
+
+# flagged units on both sides of the confirmation's ranges: a block's 32 sectors, 2048 blocks of them, two passes each
+@pytest.mark.parametrize("flagged", [0, 1, 31, 33, 2048 * 32 - 1, 2048 * 32, 2048 * 32 + 1, 2048 * 64 + 5])
+def test_record_offsets_at_range_edges(flagged):
+    masters = _random(8 * SECTOR, 4).view(8, SECTOR)
+    masters[5], masters[6] = masters[2], masters[2]   # three records for master 2, 5 and 6
+    idx = carve.build_master_index(masters.view(-1), [0, 8])
+    n = 2048 * 64 + 300
+    image = torch.zeros(n, SECTOR, dtype=torch.uint8, device="cuda")
+    places = torch.from_numpy(np.sort(np.random.default_rng(flagged).permutation(n)[:flagged])).cuda()
+    which = torch.arange(flagged, device="cuda") % 8
+    image[places] = masters[which]
+    sc = carve.scan_image(idx, image.view(-1), tau_mode=carve.CARVE_TAU_ANY)
+    assert carve.flagged_sectors(sc).numel() == flagged
+    rec = carve.confirm_matches(idx, sc)
+    triple = ((which == 2) | (which == 5) | (which == 6)).cpu().numpy()
+    repeat = np.where(triple, 3, 1)
+    assert np.array_equal(rec["disk_sector"].astype(np.int64), np.repeat(places.cpu().numpy(), repeat))
+    master = [[2, 5, 6] if t else [int(w)] for t, w in zip(triple, which.tolist())]
+    assert np.array_equal(rec["sector_in_file"], np.array(sum(master, []), dtype=np.uint32))

@@ -68,11 +68,15 @@ static_assert((2 * kNoAllocMaxWords + 2 * kNoAllocMaxChunks) % carve::kCtrStride
 
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;   // master whose key could not be placed
 
-// A scan object's device counters: [0] flagged units, [1] confirmed records,
-// [kConfirmedWord] 1 once a confirmation ran after the latest scan. Every
-// scan's compaction clears the marker on the device, so a scan replayed from a
-// captured graph (which runs no host code) still invalidates an earlier
-// confirmation; the host checks it before reusing one.
+// A scan object's counters: [0] flagged units, [1] confirmed records,
+// [kConfirmedWord] 1 once a confirmation ran after the latest scan. The first
+// two are kept on the device, where later kernels read them, and all three in
+// pinned host memory, written there by the kernels that finish them: the host
+// reads them after a synchronization with no copy enqueued for it (a 64 MiB
+// disk's step 51 -> 48 us together with the scan's ordering event, below). Every
+// scan's compaction clears the marker, so a scan replayed from a captured graph
+// (which runs no host code) still invalidates an earlier confirmation; the
+// host checks it before reusing one.
 constexpr uint32_t kConfirmedWord = 2;
 
 // Timed launches whose kernel durations a scan object keeps (the most recent).
@@ -212,7 +216,7 @@ struct IdsOut {
   uint64_t* img_off;   // batches: n_images + 1 positions
   uint64_t cap;        // room in ids (and img_of)
   uint64_t* total;     // receives the count
-  uint64_t* clear;     // the confirmation marker to clear, or null (see kConfirmedWord)
+  uint64_t* host;      // the scan object's counters in host memory, or null
 };
 template <class Src, int kItems, bool kDirect>
 __global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint64_t* __restrict__ words, uint64_t n,
@@ -272,7 +276,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint6
   const bool last = c == gridDim.x - 1;
   if (last && t == 0) {
     *out.total = base + all;
-    if (out.clear) *out.clear = 0;
+    if (out.host) {
+      out.host[0] = base + all;
+      out.host[kConfirmedWord] = 0;
+    }
   }
   // the images the chunk's words belong to (uniform searches)
   uint32_t im0 = 0, im1 = 0;
@@ -420,6 +427,12 @@ __global__ void k_stage_out(const uint64_t* __restrict__ counts, int with_matche
 __global__ void k_fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
     p[i] = v;
+}
+
+// The counters of a scan of nothing.
+__global__ void k_clear_counts(uint64_t* count, uint64_t* host) {
+  count[0] = count[1] = 0;
+  host[0] = host[1] = host[kConfirmedWord] = 0;
 }
 
 struct NonEmptyLists {
@@ -702,10 +715,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_confirm_count(Src src, const 
                                                                 const uint32_t* __restrict__ hit_slot, ConfirmView cv,
                                                                 uint32_t* __restrict__ n_match,
                                                                 uint64_t* __restrict__ match_mask,
-                                                                uint64_t* __restrict__ range_sums,
-                                                                uint64_t* __restrict__ confirmed) {
+                                                                uint64_t* __restrict__ range_sums) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *confirmed = 1;   // stream order: after the scan that cleared it
   constexpr uint32_t kLanes = confirm_lanes<Src>();
   constexpr uint64_t kGroupMask = (1ull << kLanes) - 1ull;
   const UnitRange range = confirm_range<Src>(count.get());
@@ -816,7 +827,8 @@ __device__ __forceinline__ void put_record(carve_batch_match* out, uint64_t pos,
 // Thread per flagged unit of the block's range (the ranges of
 // k_confirm_count, so the same grid): its confirmed matches, in candidate (=
 // file, sector-in-file) order, behind those of the units before it; records
-// past `cap` are counted but not written. *total receives the number of records.
+// past `cap` are counted but not written. *total and host[1] receive the number
+// of records, host[kConfirmedWord] the mark (see kConfirmedWord).
 template <class Src, class Rec>
 __global__ __launch_bounds__(kBlockThreads) void k_confirm_emit(Src src, const uint64_t* __restrict__ ids,
                                                                const uint32_t* __restrict__ img_of, Count count,
@@ -825,12 +837,18 @@ __global__ __launch_bounds__(kBlockThreads) void k_confirm_emit(Src src, const u
                                                                const uint64_t* __restrict__ match_mask,
                                                                const uint64_t* __restrict__ range_sums,
                                                                Rec* __restrict__ out, uint64_t cap,
-                                                               uint64_t* __restrict__ total) {
+                                                               uint64_t* __restrict__ total,
+                                                               uint64_t* __restrict__ host) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
   const uint64_t n_flagged = count.get();
   const UnitRange range = confirm_range<Src>(n_flagged);
+  auto finish = [&](uint64_t records) {
+    *total = records;
+    host[1] = records;
+    host[kConfirmedWord] = 1;
+  };
   if (range.begin >= range.end) {
-    if (n_flagged == 0 && blockIdx.x == 0 && threadIdx.x == 0) *total = 0;
+    if (n_flagged == 0 && blockIdx.x == 0 && threadIdx.x == 0) finish(0);
     return;
   }
   uint64_t s = 0, before;
@@ -871,7 +889,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_confirm_emit(Src src, const u
       if (eq) put_record(out, pos++, f.j, cv.m_file[m], cv.m_k[m], f.image);
     }
   }
-  if (range.end == n_flagged && threadIdx.x == 0) *total = before;
+  if (range.end == n_flagged && threadIdx.x == 0) finish(before);
 }
 
 // Copies ids [0, min(*count, cap)); cap is at most the ids the scan has room for.
@@ -1195,7 +1213,7 @@ struct carve_scan {
   std::vector<ImageDesc> uploaded;
   DevBuf bitmap, ws, ids, img_of, count, hit_slot, img_off;   // hit_slot: matched slot of each flagged sector
   DevBuf tau_words;   // one image, per-cluster rule: the hit words of the position-split scan
-  HostBuf h_small, h_img_off;                                 // pinned readbacks
+  HostBuf h_count, h_img_off;                                 // pinned: the counters, a readback
   // confirmation: records go to `matches` (rec_cap of them) or to a caller's
   // device buffer (conf_dest, conf_dest_cap records)
   DevBuf n_match, match_mask, matches, range_sums;
@@ -1209,7 +1227,10 @@ struct carve_scan {
   // timing: launch k brackets its scan kernel with ev[2 (k mod kTimedRing)]
   // and ev[2 (k mod kTimedRing) + 1]; n_timed launches so far
   std::vector<hipEvent_t> ev;
-  hipEvent_t kernel_done = nullptr;   // recorded after each scan kernel, before the compaction (scan_wait_kernel)
+  // recorded after each scan kernel, before the compaction, once scan_wait_kernel has been called: the
+  // record costs the stream about 4 us between the two
+  hipEvent_t kernel_done = nullptr;
+  bool launched = false;   // a scan kernel was enqueued
   uint64_t n_timed = 0;
   bool timing = false, timed = false;
 };
@@ -1234,16 +1255,6 @@ bool use_split(const carve_index* idx, uint32_t any_tau) {
   if (idx->cfg.split == CARVE_SPLIT_OFF) return false;
   return idx->log2_bloom_words >= kSplitMinLog2;
 }
-
-// n (at most 8) consecutive device words, in one copy.
-int read_words(carve_scan* sc, const uint64_t* d, uint32_t n, uint64_t* h) {
-  CARVE_TRY(sc->h_small.reserve(64));
-  HIP_TRY(hipMemcpyAsync(sc->h_small.p, d, 8 * n, hipMemcpyDeviceToHost, sc->stream));
-  HIP_TRY(hipStreamSynchronize(sc->stream));
-  for (uint32_t i = 0; i < n; ++i) h[i] = sc->h_small.as<uint64_t>()[i];
-  return CARVE_OK;
-}
-int read_u64(carve_scan* sc, const uint64_t* d, uint64_t* h) { return read_words(sc, d, 1, h); }
 
 // Memory a kernel may read: device (or managed) memory, not host memory.
 bool gpu_readable(const void* p) {
@@ -1322,7 +1333,7 @@ int launch_scan(carve_scan* sc, const Src& src) {
   const uint64_t n_words = sc->n_tiles;
   uint64_t* d_count = sc->count.as<uint64_t>();
   if (n_words == 0) {   // nothing to scan: the count is zero (and the confirmation marker cleared)
-    k_fill_u64<<<1, 64, 0, s>>>(d_count, kConfirmedWord + 1, 0);
+    k_clear_counts<<<1, 1, 0, s>>>(d_count, sc->h_count.as<uint64_t>());
     if (sc->batch) k_fill_u64<<<1, 256, 0, s>>>(sc->img_off.as<uint64_t>(), sc->n_images + 1, 0);
     HIP_TRY(hipGetLastError());
     return CARVE_OK;
@@ -1366,13 +1377,14 @@ int launch_scan(carve_scan* sc, const Src& src) {
     ++sc->n_timed;
     sc->timed = true;
   }
-  HIP_TRY(hipEventRecord(sc->kernel_done, s));
+  sc->launched = true;
+  if (sc->kernel_done) HIP_TRY(hipEventRecord(sc->kernel_done, s));
   const IdsOut out{sc->ids.as<uint64_t>(),
                    sc->batch ? sc->img_of.as<uint32_t>() : nullptr,
                    sc->batch ? sc->img_off.as<uint64_t>() : nullptr,
                    ~0ull,
                    d_count,
-                   d_count + kConfirmedWord};
+                   sc->h_count.as<uint64_t>()};
   if (split)   // the position-split scan's words, merged into the bitmap while counting
     launch_ids(src, sc->bitmap.as<uint64_t>(), n_words, sc->ws.as<uint64_t>(), out, s,
                TauMergeItems{sc->tau_words.as<uint64_t>(), cdiv(n_words, kPositions), sc->bitmap.as<uint64_t>(),
@@ -1412,19 +1424,22 @@ int reserve_scan(carve_scan* sc) {
     CARVE_TRY(sc->img_off.reserve((sc->n_images + 1) * 8));
   }
   if (sc->timing && sc->ev.empty()) CARVE_TRY(create_timing_ring(sc));
-  // an ordering point for other streams only (no host read, no data handed
-  // over), so without the system-scope fence that writes back and invalidates
-  // the caches at every record
-  if (!sc->kernel_done)
-    HIP_TRY(hipEventCreateWithFlags(&sc->kernel_done, hipEventDisableTiming | hipEventDisableSystemFence));
+  CARVE_TRY(sc->h_count.reserve(64));
   return CARVE_OK;
 }
 
-// The scan's counts in one readback: flagged units, confirmed records, and
-// the marker (1: a confirmation ran after the latest scan).
+// Waits for the scan's stream; the scan's counts: flagged units, confirmed
+// records, and the marker (1: a confirmation ran after the latest scan).
 int read_counts(carve_scan* sc, uint64_t c[3]) {
-  static_assert(kConfirmedWord == 2, "the counts and the marker are read in one copy");
-  return read_words(sc, sc->count.as<uint64_t>(), 3, c);
+  HIP_TRY(hipStreamSynchronize(sc->stream));
+  for (int i = 0; i < 3; ++i) c[i] = sc->h_count.as<volatile uint64_t>()[i];
+  return CARVE_OK;
+}
+int read_flagged(carve_scan* sc, uint64_t* n) {
+  uint64_t c[3];
+  CARVE_TRY(read_counts(sc, c));
+  *n = c[0];
+  return CARVE_OK;
 }
 
 // Confirmation buffers for up to cap_f flagged units. Records: room for
@@ -1450,7 +1465,7 @@ void launch_confirm_emit(carve_scan* sc, const Src& src, const ConfirmView& cv, 
   k_confirm_emit<Src, Rec><<<sc->conf_grid, kBlockThreads, 0, sc->stream>>>(
       src, sc->ids.as<uint64_t>(), sc->batch ? sc->img_of.as<uint32_t>() : nullptr, nf, sc->hit_slot.as<uint32_t>(),
       cv, sc->n_match.as<uint32_t>(), sc->match_mask.as<uint64_t>(), sc->range_sums.as<uint64_t>(), out, cap,
-      sc->count.as<uint64_t>() + 1);
+      sc->count.as<uint64_t>() + 1, sc->h_count.as<uint64_t>());
 }
 
 // Enqueue the confirmation of every flagged unit of the scan: the equal
@@ -1492,7 +1507,7 @@ int confirm_enqueue_impl(const carve_index* idx, carve_scan* sc, const Src& src,
   sc->conf_grid = most_ranges < kConfirmRanges ? (uint32_t)most_ranges : kConfirmRanges;
   k_confirm_count<Src><<<sc->conf_grid, kBlockThreads, 0, s>>>(
       src, sc->ids.as<uint64_t>(), img_of, nf, sc->hit_slot.as<uint32_t>(), cv, sc->n_match.as<uint32_t>(),
-      sc->match_mask.as<uint64_t>(), sc->range_sums.as<uint64_t>(), sc->count.as<uint64_t>() + kConfirmedWord);
+      sc->match_mask.as<uint64_t>(), sc->range_sums.as<uint64_t>());
   launch_confirm_emit(sc, src, cv, nf, dest ? dest : sc->matches.as<Rec>(), dest ? dest_cap : rec_cap);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
@@ -1950,7 +1965,7 @@ extern "C" void free_scan(carve_scan* sc) {
                     &sc->matches})
     b->release();
   sc->h_desc.release();
-  sc->h_small.release();
+  sc->h_count.release();
   sc->h_img_off.release();
   for (hipEvent_t e : sc->ev) (void)hipEventDestroy(e);
   if (sc->kernel_done) (void)hipEventDestroy(sc->kernel_done);
@@ -2225,9 +2240,9 @@ extern "C" int flagged_sectors(carve_scan* sc, uint64_t* out, uint64_t cap, uint
   uint64_t n = 0;
   if (cap && sc->n_tiles && is_device_memory(out)) {   // copy on the device, then one synchronization
     CARVE_TRY(enqueue_id_copy(sc, out, cap));
-    CARVE_TRY(read_u64(sc, sc->count.as<uint64_t>(), &n));
+    CARVE_TRY(read_flagged(sc, &n));
   } else {
-    CARVE_TRY(read_u64(sc, sc->count.as<uint64_t>(), &n));
+    CARVE_TRY(read_flagged(sc, &n));
     CARVE_TRY(copy_ids(sc, 0, n, out, cap));
   }
   *n_out = n;
@@ -2247,7 +2262,16 @@ extern "C" int flagged_sectors_enqueue(carve_scan* sc, uint64_t* out, uint64_t c
 
 extern "C" int scan_wait_kernel(carve_scan* sc, void* stream) {
   if (!sc) return fail(CARVE_EINVAL, "scan_wait_kernel: null scan");
-  if (!sc->kernel_done) return CARVE_OK;   // no scan kernel enqueued yet
+  if (!sc->launched) return CARVE_OK;   // no scan kernel enqueued yet
+  if (!sc->kernel_done) {
+    // The first call: the latest scan kernel's end was not recorded, so this
+    // wait is for all the scan's stream holds so far; later scans record it.
+    // An ordering point for other streams only (no host read, no data handed
+    // over), so without the system-scope fence that writes back and
+    // invalidates the caches at every record.
+    HIP_TRY(hipEventCreateWithFlags(&sc->kernel_done, hipEventDisableTiming | hipEventDisableSystemFence));
+    HIP_TRY(hipEventRecord(sc->kernel_done, sc->stream));
+  }
   HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, sc->kernel_done, 0));
   return CARVE_OK;
 }
@@ -2329,7 +2353,7 @@ extern "C" int batch_flagged_sectors(carve_batch* b, uint32_t image, uint64_t* o
   if (cap && !out) return fail(CARVE_EINVAL, "batch_flagged_sectors: null out with cap > 0");
   uint64_t first = 0, n = 0;
   if (all) {
-    if (b->n_tiles) CARVE_TRY(read_u64(b, b->count.as<uint64_t>(), &n));
+    if (b->n_tiles) CARVE_TRY(read_flagged(b, &n));
   } else {
     CARVE_TRY(read_img_off(b));
     const uint64_t* off = b->h_img_off.as<uint64_t>();

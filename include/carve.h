@@ -107,7 +107,9 @@ typedef struct {
 } carve_image_desc;        /* 24 bytes */
 
 typedef struct {
-  uint32_t blocks_per_cu;   /* work-groups of the persistent scan grid per compute unit; 0 = as many as fit */
+  uint32_t blocks_per_cu;   /* work-groups of the persistent scan grid per compute unit; 0 = no cap: as many as
+                               serve the scan (a djb2 scan that does not ask for runs of tiles either is then
+                               launched with a wave per 16 sectors, which the hardware hands out) */
   uint32_t tiles_per_chunk; /* consecutive 64-sector tiles a wave takes before striding (the split walk also
                                hands out the last eighth of each position's tiles in runs of this length); 0 = 1 */
   uint32_t split;           /* carve_split_mode: how scans of one image under the per-cluster rule walk it */
@@ -118,7 +120,8 @@ typedef struct {
  * cluster position: position p's sectors only need S_p, so the chip's 8 XCDs
  * each scan one position and keep one eighth of the prefilter in their L2. */
 typedef enum {
-  CARVE_SPLIT_AUTO = 0,     /* split when the prefilter is 4 MiB or more (too large for one XCD's L2) */
+  CARVE_SPLIT_AUTO = 0,     /* split when the prefilter is 8 MiB or more (too large for one XCD's L2) and the
+                               image larger than 512 MiB */
   CARVE_SPLIT_OFF = 1,      /* always scan contiguously */
   CARVE_SPLIT_ON = 2        /* always split (when the index has a prefilter) */
 } carve_split_mode;

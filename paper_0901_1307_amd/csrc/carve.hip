@@ -66,6 +66,8 @@ static_assert(kNoAllocMaxChunks * kItemsPerBlock == kNoAllocMaxWords, "scratch h
 static_assert(kNoAllocCounters == carve::kTauCounters, "scratch holds the split scan's counters");
 static_assert((2 * kNoAllocMaxWords + 2 * kNoAllocMaxChunks) % carve::kCtrStride == 0, "counters on 256-byte lines");
 
+constexpr uint64_t kDirectWords = 16384;   // hit words compacted by one launch (launch_ids)
+
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;   // master whose key could not be placed
 
 // A scan object's counters: [0] flagged units, [1] confirmed records,
@@ -512,13 +514,14 @@ __global__ void k_bloom_build(const uint64_t* __restrict__ keys, uint64_t n_slot
 // The filter split by cluster position: slice t holds the keys with a master
 // at position t (placed like the whole filter, in 2^log2_words words). Built
 // for every sector index with a filter. A filter of 2^kSplitMinLog2 words
-// (4 MiB) or more cannot stay in an XCD's 4 MB L2 beside the streamed image,
-// so per-cluster scans of one image run position-split (k_scan_tau) by
-// default, each XCD holding one eighth; smaller filters stay in L2 whole and
-// the contiguous scan is faster with them (1.29 vs 1.35 ms on the 8 GiB mid
-// workload, 2 MiB filter; the split took the 64 GiB large workload, 8 MiB
-// filter, from 11.79 to 10.86 ms). carve_scan_config.split overrides it.
-constexpr uint32_t kSplitMinLog2 = 19;
+// (8 MiB) or more cannot stay in an XCD's 4 MB L2 beside the streamed image,
+// so per-cluster scans of one image run position-split by default, each XCD
+// holding one eighth. Scan kernels contiguous / split: with a 4 MiB filter
+// (4 M masters) 700 MiB 114 / 116 us, 4 GiB 645 / 645; with 8 MiB (16 M
+// masters) 256 MiB 49 / 46, 1 GiB 180 / 171, 4 GiB 700 / 675. The split costs
+// a launch more where the compaction would take one (about 4 us up to 512 MiB),
+// so it starts above that. carve_scan_config.split overrides it.
+constexpr uint32_t kSplitMinLog2 = 20;
 __global__ void k_bloom_tau_build(const uint64_t* __restrict__ keys, const uint8_t* __restrict__ tau_mask,
                                   uint64_t n_slots, uint32_t log2_words, uint64_t* bloom_tau) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -974,31 +977,10 @@ struct HostBuf {
 
 uint64_t cdiv(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
-// Device address, on the current device, of djb2's digit-plane weight table
-// (0 on failure).
-uint64_t weight_table() {
-  static uint64_t ptr[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (!ptr[dev]) {
-    void* p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_weights)) != hipSuccess) return 0;
-    ptr[dev] = (uint64_t)(uintptr_t)p;
-  }
-  return ptr[dev];
-}
-
-// The table argument of the scan kernel for a signature kind: djb2's weights;
-// the CRC needs none. Returns false when the table is unavailable.
-bool sig_table(uint32_t kind, uint64_t* wt) {
-  *wt = kind == CARVE_SIG_CRC64_ISO ? 0 : weight_table();
-  return kind == CARVE_SIG_CRC64_ISO || *wt != 0;
-}
-
 // One scan kernel launch for the signature kind chosen at run time.
 template <int kMode, class Src>
 int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
-                  const IndexView& ix, uint64_t wt, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
+                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
                   uint32_t layout = CARVE_LAYOUT_BUCKETED);
 
 int device_cus() {
@@ -1065,34 +1047,53 @@ int scan_counts(const uint32_t* in, T* out, uint64_t n, uint64_t* d_total, DevBu
   return CARVE_OK;
 }
 
+// A djb2 scan takes the kernels with a wave per 16 sectors unless its launch
+// shape asks for something else (a cap on the grid, runs of tiles), or its grid
+// would be too large.
+template <int kSig>
+bool scan_by_parts(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
+  return kSig == kSigDjb2 && !per_cu_cap && chunk <= 1 && n_tiles * kTileParts <= kMaxPartBlocks;
+}
+// The CRC's persistent grid when the launch shape leaves it open: 2 blocks per
+// CU, half of what fits (2 GiB: 324 against 339 us, 64 MiB the same).
+constexpr uint32_t kCrcBlocksPerCu = 2;
+
 template <int kMode, int kSig, int kLayout, class Src>
-void launch_k_scan_as(const Src& src, uint64_t want, uint32_t chunk, uint32_t per_cu_cap, const IndexView& ix,
-                      uint64_t wt, uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
+void launch_k_scan_as(const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap, const IndexView& ix,
+                      uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
+  if constexpr (kSig == kSigDjb2) {
+    if (scan_by_parts<kSig>(per_cu_cap, chunk, n_tiles)) {
+      k_scan_parts<kMode, Src, kLayout><<<(unsigned)(n_tiles * kTileParts), kWave, 0, s>>>(src, ix, out, hit_slot);
+      return;
+    }
+  } else if (!per_cu_cap) {
+    per_cu_cap = kCrcBlocksPerCu;
+  }
+  const uint64_t want = cdiv(cdiv(n_tiles, chunk), kScanWaves);
   const int grid = resident_grid(k_scan<kMode, kSig, Src, kLayout>, kScanThreads, want, per_cu_cap);
-  k_scan<kMode, kSig, Src, kLayout><<<grid, kScanThreads, 0, s>>>(src, chunk, ix, wt, out, hit_slot);
+  k_scan<kMode, kSig, Src, kLayout><<<grid, kScanThreads, 0, s>>>(src, chunk, ix, out, hit_slot);
 }
 
 template <int kMode, int kSig, class Src>
-void launch_k_scan_sig(uint32_t layout, const Src& src, uint64_t want, uint32_t chunk, uint32_t per_cu_cap,
-                       const IndexView& ix, uint64_t wt, uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
+void launch_k_scan_sig(uint32_t layout, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
+                       const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
   if constexpr (kMode == kFlags || kMode == kFlagBits) {
     if (layout == CARVE_LAYOUT_LINEAR)
-      return launch_k_scan_as<kMode, kSig, kLayoutLinear>(src, want, chunk, per_cu_cap, ix, wt, out, hit_slot, s);
+      return launch_k_scan_as<kMode, kSig, kLayoutLinear>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
     if (layout == CARVE_LAYOUT_SORTED)
-      return launch_k_scan_as<kMode, kSig, kLayoutSorted>(src, want, chunk, per_cu_cap, ix, wt, out, hit_slot, s);
+      return launch_k_scan_as<kMode, kSig, kLayoutSorted>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
   }
-  launch_k_scan_as<kMode, kSig, kLayoutBucketed>(src, want, chunk, per_cu_cap, ix, wt, out, hit_slot, s);
+  launch_k_scan_as<kMode, kSig, kLayoutBucketed>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
 }
 
 template <int kMode, class Src>
 int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
-                  const IndexView& ix, uint64_t wt, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
+                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
                   uint32_t layout) {
-  const uint64_t want = cdiv(cdiv(n_tiles, chunk), kScanWaves);
   if (kind == CARVE_SIG_CRC64_ISO)
-    launch_k_scan_sig<kMode, kSigCrc64>(layout, src, want, chunk, per_cu_cap, ix, wt, out, hit_slot, s);
+    launch_k_scan_sig<kMode, kSigCrc64>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
   else
-    launch_k_scan_sig<kMode, kSigDjb2>(layout, src, want, chunk, per_cu_cap, ix, wt, out, hit_slot, s);
+    launch_k_scan_sig<kMode, kSigDjb2>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }
@@ -1101,28 +1102,37 @@ int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chun
 // size is a multiple of 8, one eighth of it per cluster position.
 template <int kSig, int kLayout, bool kSlots>
 void launch_k_scan_tau_as(const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk, uint32_t per_cu_cap,
-                          const IndexView& ix, uint64_t wt, uint64_t* tau_words, uint32_t* hit_slot, uint64_t* ctr,
+                          const IndexView& ix, uint64_t* tau_words, uint32_t* hit_slot, uint64_t* ctr,
                           hipStream_t s) {
+  if constexpr (kSig == kSigDjb2) {
+    if (scan_by_parts<kSig>(per_cu_cap, chunk, kPositions * words_per_pos)) {
+      k_scan_tau_parts<kLayout, kSlots><<<(unsigned)(kPositions * words_per_pos * kTileParts), kWave, 0, s>>>(
+          d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
+      return;
+    }
+  } else if (!per_cu_cap) {
+    per_cu_cap = kCrcBlocksPerCu;
+  }
   const uint64_t want = kPositions * cdiv(cdiv(words_per_pos, chunk), kScanWaves);
   int grid = resident_grid(k_scan_tau<kSig, kLayout, kSlots>, kScanThreads, want, per_cu_cap);
   grid = grid < (int)kPositions ? (int)kPositions : grid - grid % (int)kPositions;
   k_fill_u64<<<1, 256, 0, s>>>(ctr, kTauCounters, 0);   // the work-sharing counters start at zero
   k_scan_tau<kSig, kLayout, kSlots><<<grid, kScanThreads, 0, s>>>(d.base, d.n_sectors, d.tau0, words_per_pos, chunk,
-                                                                   ix, wt, tau_words, hit_slot,
+                                                                   ix, tau_words, hit_slot,
                                                                    (unsigned int*)ctr);
 }
 
 template <int kSig, bool kSlots>
 void launch_k_scan_tau_sig(uint32_t layout, const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk,
-                           uint32_t per_cu_cap, const IndexView& ix, uint64_t wt, uint64_t* tau_words,
+                           uint32_t per_cu_cap, const IndexView& ix, uint64_t* tau_words,
                            uint32_t* hit_slot, uint64_t* ctr, hipStream_t s) {
   if (layout == CARVE_LAYOUT_LINEAR)
-    return launch_k_scan_tau_as<kSig, kLayoutLinear, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    return launch_k_scan_tau_as<kSig, kLayoutLinear, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                               hit_slot, ctr, s);
   if (layout == CARVE_LAYOUT_SORTED)
-    return launch_k_scan_tau_as<kSig, kLayoutSorted, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    return launch_k_scan_tau_as<kSig, kLayoutSorted, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                               hit_slot, ctr, s);
-  launch_k_scan_tau_as<kSig, kLayoutBucketed, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+  launch_k_scan_tau_as<kSig, kLayoutBucketed, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                        hit_slot, ctr, s);
 }
 
@@ -1138,18 +1148,18 @@ uint64_t* tau_counters(uint64_t* tau_words, uint64_t n_words) {
 // hit_slot null: no slot records (the flags are not confirmed afterwards). ctr: kTauCounters
 // words, 256-byte aligned, for the work-sharing counters (cleared here).
 int launch_k_scan_tau(uint32_t kind, uint32_t layout, const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk,
-                      uint32_t per_cu_cap, const IndexView& ix, uint64_t wt, uint64_t* tau_words, uint32_t* hit_slot,
+                      uint32_t per_cu_cap, const IndexView& ix, uint64_t* tau_words, uint32_t* hit_slot,
                       uint64_t* ctr, hipStream_t s) {
   const bool crc = kind == CARVE_SIG_CRC64_ISO;
   if (hit_slot) {
-    if (crc) launch_k_scan_tau_sig<kSigCrc64, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    if (crc) launch_k_scan_tau_sig<kSigCrc64, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                      hit_slot, ctr, s);
-    else launch_k_scan_tau_sig<kSigDjb2, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    else launch_k_scan_tau_sig<kSigDjb2, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                 hit_slot, ctr, s);
   } else {
-    if (crc) launch_k_scan_tau_sig<kSigCrc64, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    if (crc) launch_k_scan_tau_sig<kSigCrc64, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                       nullptr, ctr, s);
-    else launch_k_scan_tau_sig<kSigDjb2, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, wt, tau_words,
+    else launch_k_scan_tau_sig<kSigDjb2, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
                                                  nullptr, ctr, s);
   }
   HIP_TRY(hipGetLastError());
@@ -1169,7 +1179,6 @@ struct carve_index {
   uint32_t zero_sig_mask = 0;
   uint64_t n_unique = 0;
   uint64_t n_overflow = 0;
-  uint64_t weights = 0;     // djb2's weight table (0 for the CRC)
   uint32_t sig_kind = CARVE_SIG_DJB2_64;
   uint32_t unit_bytes = kSectorBytes;   // master units: sectors, or 64-byte fragments
   uint32_t log2_bloom_words = 0;
@@ -1242,18 +1251,19 @@ OneImage one_image(const carve_scan* sc) { return OneImage{sc->desc[0]}; }
 
 // Whether a scan of one image under rule any_tau runs position-split
 // (k_scan_tau): never for the any-position rule or without the split filter;
-// else as the index's scan config says (automatic: filters of 4 MiB and more).
-bool use_split(const carve_index* idx, uint32_t any_tau);
+// else as the index's scan config says (automatic: filters of 8 MiB and more,
+// and images past kDirectWords, whose compaction needs its first kernel anyway).
+bool use_split(const carve_index* idx, uint32_t any_tau, uint64_t n_words);
 FragmentWindows fragment_windows(const carve_scan* sc) { return FragmentWindows{sc->desc[0]}; }
 ManyImages many_images(const carve_scan* sc) {
   return ManyImages{sc->d_desc.as<ImageDesc>(), sc->n_images};
 }
 
-bool use_split(const carve_index* idx, uint32_t any_tau) {
+bool use_split(const carve_index* idx, uint32_t any_tau, uint64_t n_words) {
   if (any_tau || !idx->bloom_tau.bytes) return false;
   if (idx->cfg.split == CARVE_SPLIT_ON) return true;
   if (idx->cfg.split == CARVE_SPLIT_OFF) return false;
-  return idx->log2_bloom_words >= kSplitMinLog2;
+  return idx->log2_bloom_words >= kSplitMinLog2 && n_words > kDirectWords;
 }
 
 // Memory a kernel may read: device (or managed) memory, not host memory.
@@ -1299,7 +1309,6 @@ int validate_image(const void* image, uint64_t n_bytes, uint32_t tau0, uint32_t 
 // words, about a microsecond more than its own. Past that the chunk sums first,
 // and in k_emit_ids up to kSummedChunks of them per block; chunks of 1024 words
 // keep enough blocks to fill the chip, larger scans take chunks of 4096.
-constexpr uint64_t kDirectWords = 16384;
 constexpr uint64_t kSummedChunks = 4096;
 template <class Src, class Items>
 void launch_ids(const Src& src, const uint64_t* words, uint64_t n, uint64_t* ws, const IdsOut& out, hipStream_t s,
@@ -1343,7 +1352,7 @@ int launch_scan(carve_scan* sc, const Src& src) {
   ImageDesc one{};
   if constexpr (std::is_same<Src, OneImage>::value) {
     one = src.d;
-    split = use_split(idx, one.any_tau);
+    split = use_split(idx, one.any_tau, n_words);
   }
   const uint64_t slot = 2 * (sc->n_timed % kTimedRing);
   if (sc->timing) HIP_TRY(hipEventRecord(sc->ev[slot], s));
@@ -1363,13 +1372,13 @@ int launch_scan(carve_scan* sc, const Src& src) {
   } else if (split) {
     const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
     CARVE_TRY(launch_k_scan_tau(idx->sig_kind, idx->layout, one, cdiv(n_words, kPositions), chunk,
-                                per_cu, idx->view(), idx->weights, sc->tau_words.as<uint64_t>(),
+                                per_cu, idx->view(), sc->tau_words.as<uint64_t>(),
                                 sc->hit_slot.as<uint32_t>(), tau_counters(sc->tau_words.as<uint64_t>(), n_words),
                                 s));
   } else {
     const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
     CARVE_TRY(launch_k_scan<kFlags>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(),
-                                     idx->weights, sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>(), s,
+                                     sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>(), s,
                                      idx->layout));
   }
   if (sc->timing) {
@@ -1414,7 +1423,7 @@ int reserve_scan(carve_scan* sc) {
   CARVE_TRY(sc->ids.reserve(n_words * kTileSectors * 8));
   // a single image of sectors may be scanned split by position (k_scan_tau):
   // its tiles of 64 clusters reach slot 512 * ceil(n_words / 8)
-  const bool split = !sc->batch && !sc->fragments && sc->idx && use_split(sc->idx, sc->desc[0].any_tau);
+  const bool split = !sc->batch && !sc->fragments && sc->idx && use_split(sc->idx, sc->desc[0].any_tau, sc->n_tiles);
   const uint64_t tau_tiles = cdiv(n_words, kPositions);
   CARVE_TRY(sc->hit_slot.reserve((split ? tau_tiles * kPositions : n_words) * kTileSectors * 4));
   if (split) CARVE_TRY(sc->tau_words.reserve((tau_counter_offset(n_words) + kTauCounters) * 8));
@@ -1581,10 +1590,8 @@ extern "C" int sector_signatures_kind(uint32_t sig_kind, const void* sectors, ui
   if (!sectors || !sigs) return fail(CARVE_EINVAL, "sector_signatures: null pointer");
   if ((uintptr_t)sectors % 16) return fail(CARVE_EINVAL, "sector_signatures: sectors not 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  uint64_t wt = 0;
-  if (!sig_table(sig_kind, &wt)) return fail(CARVE_EDEVICE, "sector_signatures: weight table unavailable");
   const OneImage src{ImageDesc{(const uint8_t*)sectors, n_sectors, 0, 0, 0}};
-  return launch_k_scan<kSigs>(sig_kind, src, cdiv(n_sectors, kTileSectors), 1, 0, IndexView{}, wt, sigs, nullptr, s);
+  return launch_k_scan<kSigs>(sig_kind, src, cdiv(n_sectors, kTileSectors), 1, 0, IndexView{}, sigs, nullptr, s);
 }
 
 extern "C" int sector_signatures(const void* sectors, uint64_t n_sectors, uint64_t* sigs, void* stream) {
@@ -1748,8 +1755,6 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
   ix->masters = (const uint8_t*)master_sectors;
   ix->unit_bytes = unit;
   ix->sig_kind = p.sig_kind;
-  if (!sig_table(p.sig_kind, &ix->weights))
-    return bail(fail(CARVE_EDEVICE, "build_master_index: weight table unavailable"));
   ix->layout = p.layout;
   // the bucketed table holds the candidate lists in every layout; max_load
   // sizes the layout that is probed
@@ -1808,7 +1813,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     } else {
       const uint64_t n_tiles = cdiv(n_masters, kTileSectors);
       const OneImage src{ImageDesc{ix->masters, n_masters, 0, 0, 0}};
-      if ((rc = launch_k_scan<kSigs>(ix->sig_kind, src, n_tiles, 1, 0, IndexView{}, ix->weights, sig.as<uint64_t>(),
+      if ((rc = launch_k_scan<kSigs>(ix->sig_kind, src, n_tiles, 1, 0, IndexView{}, sig.as<uint64_t>(),
                                      nullptr, s)))
         return bail2(rc);
     }
@@ -2068,14 +2073,14 @@ extern "C" int scan_image_noalloc(const carve_index* idx, const void* image, uin
   const uint32_t per_cu = idx->cfg.blocks_per_cu;
   const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
   const IdsOut out{ids, nullptr, nullptr, cap, count, nullptr};
-  if (use_split(idx, src.d.any_tau)) {   // as scan_image: the position-split scan
+  if (use_split(idx, src.d.any_tau, n_words)) {   // as scan_image: the position-split scan
     CARVE_TRY(launch_k_scan_tau(idx->sig_kind, idx->layout, src.d, cdiv(n_words, kPositions), chunk, per_cu,
-                                idx->view(), idx->weights, tau_words, nullptr, ctr, s));
+                                idx->view(), tau_words, nullptr, ctr, s));
     launch_ids(src, bitmap, n_words, sums, out, s,
                TauMergeItems{tau_words, cdiv(n_words, kPositions), bitmap, n_words, tau0,
                              (uint32_t)(n_sectors % kTileSectors)}, true);
   } else {
-    CARVE_TRY(launch_k_scan<kFlagBits>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(), idx->weights, bitmap,
+    CARVE_TRY(launch_k_scan<kFlagBits>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(), bitmap,
                                         nullptr, s, idx->layout));
     launch_ids(src, bitmap, n_words, sums, out, s, PopcountItems{bitmap}, false);
   }
@@ -2662,7 +2667,7 @@ extern "C" int autotune_index(const void* master_sectors, const uint64_t* file_s
       ++res.candidates;
       float cand_ms = 1e30f;
       for (uint32_t w : split_modes(ix, contiguous)) {
-        ix->cfg = carve_scan_config{2, 1, w, 0};
+        ix->cfg = carve_scan_config{0, 1, w, 0};
         float ms = 0.f;
         if ((rc = time_walk(ix, sample_image, n_bytes, stream, contiguous, &sc, &ms)) != CARVE_OK) break;
         if (ms < cand_ms) cand_ms = ms;

@@ -3,20 +3,19 @@
 // Signature: djb2 with a 64-bit accumulator (Eq. (1), Section 2.2; 64-bit
 // accumulator, Section 4). The recurrence is linear modulo 2^64, so for a
 // 512-byte sector s_0..s_511 it unrolls to
-//     h = 5381*33^512 + sum_b s_b * 33^(511-b)            (mod 2^64).
-// Each weight 33^(511-b) mod 2^64 is split into 8 base-256 digits; with the
-// sector bytes also 8-bit, each digit plane q accumulates
-//     acc_q = sum_b s_b * digit_q(33^(511-b))
-// with v_dot4_u32_u8 (four byte products per instruction, no carry chain:
-// acc_q <= 512*255*255 < 2^25), and h = 5381*33^512 + sum_q acc_q << 8q.
-// The digits are compile-time constants (they become SGPR literals).
+//     h = 5381*33^512 + sum_b s_b * 33^(511-b)            (mod 2^64),
+// a contraction of the sector's bytes with 512 constants, done on the matrix
+// cores in 8-bit integers (djb2_phase). Each weight 33^(511-b) mod 2^64 is
+// split into 8 signed base-256 digits and each byte is taken as s_b - 128 (one
+// xor of four bytes; the 128s go into the constant), so digit plane q gives
+//     acc_q = sum_b (s_b - 128) * digit_q(33^(511-b)),   |acc_q| <= 2^23,
+// exactly, in 32 bits, and h = const + sum_q acc_q << 8q.
 //
-// Lane mapping: a wave hashes a tile of 64 sectors, one sector per lane, like
-// the paper's cohorts (Section 3.2) but 64 wide. Global loads are coalesced:
-// 8 lanes read 128 contiguous bytes of one sector (16 B each), so one load
-// instruction covers 8 full 128-byte lines. The bytes go through a per-wave
-// LDS staging area with a padded row pitch (the job Fig. 9's skewed tile did
-// for a 16-bank shared memory) and each lane reads back its own sector.
+// A wave hashes a tile of 64 sectors and ends with one sector per lane, like
+// the paper's cohorts (Section 3.2) but 64 wide. The CRC (below) is a serial
+// chain over a sector's bytes instead: there each lane runs its own sector,
+// handed to it through a per-wave LDS staging area with a padded row pitch
+// (the job Fig. 9's skewed tile did for a 16-bank shared memory).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -34,8 +33,7 @@ constexpr uint32_t kSectorBytes = 512;
 constexpr uint32_t kClusterSectors = 8;
 constexpr uint32_t kWave = 64;
 constexpr uint32_t kTileSectors = 64;                       // one sector per lane
-constexpr uint32_t kPhaseBytes = 128;                       // bytes per sector staged at once
-constexpr uint32_t kPhases = kSectorBytes / kPhaseBytes;    // 4
+constexpr uint32_t kPhaseBytes = 128;                       // the CRC: bytes per sector staged at once
 constexpr uint32_t kRowPitch = kPhaseBytes + 16;            // padding spreads rows over banks
 constexpr uint32_t kTileLds = kTileSectors * kRowPitch;     // 9216 B per wave
 constexpr uint32_t kBucketSlots = 16;                       // 16 x 8 B keys = one 128-B line
@@ -53,36 +51,49 @@ constexpr uint64_t pow33(uint32_t e) {
   return r;
 }
 
-constexpr uint64_t kInitTerm = 5381ull * pow33(kSectorBytes);   // wraps modulo 2^64
+// 5381*33^512 and 128 times the sum of all weights (the bytes enter as s - 128).
+constexpr uint64_t djb2_constant() {
+  uint64_t c = 5381ull * pow33(kSectorBytes), w = 1;
+  for (uint32_t b = 0; b < kSectorBytes; ++b, w *= 33) c += 128ull * w;
+  return c;   // wraps modulo 2^64
+}
+constexpr uint64_t kDjb2Constant = djb2_constant();
 
-// Digit plane q of the weights of bytes 4d..4d+3, packed little-endian like
-// the data dword (byte 4d is the dword's low byte).
-constexpr uint32_t weight_dword(uint32_t d, uint32_t q) {
-  uint32_t w = 0;
-  for (uint32_t k = 0; k < 4; ++k) {
-    uint64_t wb = pow33(kSectorBytes - 1 - (4 * d + k));
-    w |= (uint32_t)((wb >> (8 * q)) & 0xFFu) << (8 * k);
+// Signed base-256 digit q of w, in [-128, 127] (modulo 2^64: the carry out of
+// the last digit is dropped).
+constexpr int32_t signed_digit(uint64_t w, uint32_t q) {
+  int32_t d = 0;
+  for (uint32_t i = 0; i <= q; ++i) {
+    d = (int32_t)(w & 0xFFu);
+    if (d > 127) d -= 256;
+    w = (w - (uint64_t)(int64_t)d) >> 8;
   }
-  return w;
+  return d;
 }
 
-// All 128 x 8 weight words. They are read from device memory with uniform
-// addresses, i.e. by scalar loads of 16 words at a time; as literals they would
-// cost one scalar move per dot product, as many scalar instructions as vector ones.
-struct WeightTable {
-  uint32_t w[kSectorBytes / 4][8];
+// The weights as the matrix instruction's right operand (64 bytes deep, 16
+// columns), as each lane holds it: lane l has column n = l mod 16, depth
+// 16(l/16)..16(l/16)+15. A row of the left operand is the 16-byte pieces j, j +
+// 4, j + 8 and j + 12 of half a sector (256 bytes; j = 0..3), so one row's
+// weights are those of another times a power of 33 and need columns of their
+// own: columns 0-7 are the digit planes for one j, columns 8-15 for another,
+// in two operands: set 0 for j = 3 and 2, set 1 for j = 1 and 0.
+struct Djb2Weights {
+  uint32_t w[2][2][kWave][4];   // [set][half of the sector][lane][dword]
 };
-constexpr WeightTable make_weight_table() {
-  WeightTable t{};
-  for (uint32_t d = 0; d < kSectorBytes / 4; ++d)
-    for (uint32_t q = 0; q < 8; ++q) t.w[d][q] = weight_dword(d, q);
+constexpr Djb2Weights make_djb2_weights() {
+  Djb2Weights t{};
+  for (uint32_t set = 0; set < 2; ++set)
+    for (uint32_t half = 0; half < 2; ++half)
+      for (uint32_t l = 0; l < kWave; ++l) {
+        const uint32_t j = 3u - 2u * set - ((l >> 3) & 1u), q = l & 7u;
+        uint64_t w = pow33(kSectorBytes - 1 - (256u * half + 64u * (l >> 4) + 16u * j + 15u));
+        for (uint32_t b = 16; b-- > 0; w *= 33)
+          t.w[set][half][l][b / 4] |= (uint32_t)(signed_digit(w, q) & 0xFF) << (8 * (b % 4));
+      }
   return t;
 }
-__device__ WeightTable g_weights = make_weight_table();
-
-// Kernels take the table's address as an integer and read it through a
-// constant-address-space pointer: uniform loads from that space are scalar loads.
-typedef const __attribute__((address_space(4))) WeightTable* WeightPtr;
+__device__ const Djb2Weights g_djb2_weights = make_djb2_weights();
 
 // ------------------------------------------------------------ static for
 template <class F, int... Is>
@@ -129,18 +140,20 @@ __device__ __forceinline__ uint32_t bytes_nonzero(uint64_t x) {
 struct ContiguousRows {
   const uint8_t* base;
   uint32_t n_valid;   // 1..64
-  __device__ __forceinline__ const uint8_t* row(uint32_t s) const {
-    return base + (uint64_t)(s < n_valid ? s : n_valid - 1) * kSectorBytes;
+  __device__ __forceinline__ uint32_t offset(uint32_t s) const {
+    return (s < n_valid ? s : n_valid - 1) * kSectorBytes;
   }
+  __device__ __forceinline__ const uint8_t* row(uint32_t s) const { return base + offset(s); }
 };
 // A tile of one cluster position: sector s is base + s*4096 (the same
 // position in 64 consecutive clusters); past n_valid, the last valid one.
 struct ClusterStrideRows {
   const uint8_t* base;
   uint32_t n_valid;   // 1..64
-  __device__ __forceinline__ const uint8_t* row(uint32_t s) const {
-    return base + (uint64_t)(s < n_valid ? s : n_valid - 1) * (kClusterSectors * kSectorBytes);
+  __device__ __forceinline__ uint32_t offset(uint32_t s) const {
+    return (s < n_valid ? s : n_valid - 1) * (kClusterSectors * kSectorBytes);
   }
+  __device__ __forceinline__ const uint8_t* row(uint32_t s) const { return base + offset(s); }
 };
 
 template <bool kNonTemporal>
@@ -149,7 +162,7 @@ __device__ __forceinline__ u32x4 load16(const uint8_t* p) {
   else return *(const u32x4*)p;
 }
 
-// Phase p of a tile: instruction i, lane l loads 16 B of sector 8i + l/8 at
+// Phase p of a tile for the CRC: instruction i, lane l loads 16 B of sector 8i + l/8 at
 // byte 128p + 16(l%8); one instruction covers 8 whole 128-byte lines.
 struct PhaseRegs {
   u32x4 v[8];
@@ -162,73 +175,132 @@ __device__ __forceinline__ void load_phase(const Rows& rows, uint32_t p, PhaseRe
   for (int i = 0; i < 8; ++i) r.v[i] = load16<kNonTemporal>(rows.row(8u * i + (l >> 3)) + p * kPhaseBytes + (l & 7u) * 16u);
 }
 
-// Stage phase P through this wave's LDS area and fold its 128 bytes per
-// sector into the 8 digit-plane accumulators of lane l's sector.
-template <int P>
-__device__ __forceinline__ void hash_phase(const PhaseRegs& r, uint8_t* lds, uint64_t wt, uint32_t (&acc)[8]) {
-  // the loads issued before this call stay above it
-  __builtin_amdgcn_sched_barrier(0);
-  // The weights are loop-invariant; hiding the pointer's identity per phase
-  // keeps the compiler from hoisting all 1024 of them into scalar registers.
-  WeightPtr w = (WeightPtr)wt;
-  asm volatile("" : "+s"(w));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+
+// Sixteen sectors of a tile for the matrix path, sectors 16p..16p+15, 8 KiB:
+// load 2g + half is 256 bytes of the sectors 16p + 4g + 0..3. Lane l takes
+// sector (l/4) mod 4, its 16-byte piece 4(l/16) + l mod 4: each four
+// neighbouring lanes read 64 contiguous bytes, an instruction 8 whole 128-byte
+// lines, and the lane's bytes are already where the matrix instruction wants
+// them (row l mod 16, depth l/16), so nothing goes through LDS.
+template <bool kNonTemporal, class Rows>
+__device__ __forceinline__ void load_sectors(const Rows& rows, uint32_t p, PhaseRegs& r) {
   const uint32_t l = lane_id();
-  const uint32_t col = (l & 7u) * 16u;
+  const uint32_t at = (l >> 4) * 64u + (l & 3u) * 16u;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) *(u32x4*)(lds + (8u * i + (l >> 3)) * kRowPitch + col) = r.v[i];
-  wave_sync_lds();
-  static_for<8>([&](auto C) {
-    constexpr int c = decltype(C)::value;
-    // one 16-byte column (32 weights) at a time, or the weight loads of the
-    // whole phase get hoisted and overflow the scalar registers
-    __builtin_amdgcn_sched_barrier(0);
-    const u32x4 x4 = *(const u32x4*)(lds + l * kRowPitch + c * 16);
-    static_for<4>([&](auto K) {
-      constexpr int k = decltype(K)::value;
-      constexpr uint32_t d = P * (kPhaseBytes / 4) + c * 4 + k;
-      const uint32_t x = x4[k];
-      static_for<8>([&](auto Q) {
-        constexpr int q = decltype(Q)::value;
-        acc[q] = __builtin_amdgcn_udot4(x, w->w[d][q], acc[q], false);
-      });
-    });
-  });
-  // The accumulators must be final here: an empty asm that "modifies" them
-  // is a side effect, so neither this phase's math can sink below the next
-  // phase's LDS stores nor can those stores rise above it.
-  asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]),
-               "+v"(acc[6]), "+v"(acc[7]));
-  wave_sync_lds();
-  __builtin_amdgcn_sched_barrier(0);
+  for (int g = 0; g < 4; ++g) {
+    // a 32-bit lane offset from the tile's uniform base: no 64-bit address per load
+    const uint8_t* q = rows.base + (rows.offset(16u * p + 4u * g + ((l >> 2) & 3u)) + at);
+    r.v[2 * g] = load16<kNonTemporal>(q);
+    r.v[2 * g + 1] = load16<kNonTemporal>(q + 256);
+  }
 }
 
-__device__ __forceinline__ uint64_t finish_signature(const uint32_t (&acc)[8]) {
-  uint64_t h = kInitTerm;
+// This lane's part of the weights.
+struct Djb2Lane {
+  i32x4 w[2][2];   // [set][half]
+};
+__device__ __forceinline__ void load_djb2_lane(Djb2Lane& d) {
+  const uint32_t l = lane_id();
 #pragma unroll
-  for (int q = 0; q < 8; ++q) h += (uint64_t)acc[q] << (8 * q);
-  return h;
+  for (int set = 0; set < 2; ++set)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) d.w[set][half] = *(const i32x4*)g_djb2_weights.w[set][half][l];
+}
+
+// DPP controls: each lane takes the value of another lane of its 16.
+constexpr int kDppXor1 = 0xB1;    // quad_perm 1,0,3,2
+constexpr int kDppXor2 = 0x4E;    // quad_perm 2,3,0,1
+constexpr int kDppXor7 = 0x141;   // row_half_mirror
+constexpr int kDppXor8 = 0x128;   // row_ror 8
+template <int kCtrl>
+__device__ __forceinline__ int32_t dpp(int32_t v) {
+  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ uint64_t dpp(uint64_t v) {
+  const uint32_t lo = (uint32_t)dpp<kCtrl>((int32_t)(uint32_t)v), hi = (uint32_t)dpp<kCtrl>((int32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+// One step of a sum over lanes that also deals the values out: a lane keeps a
+// (lower) or b (upper, its partner), with the partner's added.
+template <int kCtrl, class T>
+__device__ __forceinline__ T deal_sum(T a, T b, bool upper) {
+  const T keep = upper ? b : a, send = upper ? a : b;
+  return keep + dpp<kCtrl>(send);
+}
+
+// Four sectors, two loads: the digit plane l mod 8 of sector l/16, over the
+// sector's pieces with one parity of j (lanes 0-7 of each 16 the odd ones,
+// lanes 8-15 the even ones).
+__device__ __forceinline__ int32_t djb2_planes(const u32x4& r0, const u32x4& r1, const Djb2Lane& d, bool upper) {
+  const u32x4 flip = {0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
+  const i32x4 a0 = (i32x4)(r0 ^ flip), a1 = (i32x4)(r1 ^ flip);
+  i32x4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
+  x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, d.w[0][0], x, 0, 0, 0);
+  y = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, d.w[1][0], y, 0, 0, 0);
+  x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, d.w[0][1], x, 0, 0, 0);
+  y = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, d.w[1][1], y, 0, 0, 0);
+  // the result's element j of this lane is row 4(l/16) + j: sector l/16, pieces j
+  return (upper ? x[2] : x[3]) + (upper ? y[0] : y[1]);
+}
+
+// Sixteen sectors (load_sectors): the planes' sums over the two lane pairs
+// l, l ^ 8 and l, l ^ 7, which leave a lane with one group of four sectors, the
+// one that l's bits 3 and 2 number; what is left to add are the lanes l ^ 1 and
+// l ^ 2.
+__device__ __forceinline__ uint64_t djb2_phase(const PhaseRegs& r, const Djb2Lane& d) {
+  __builtin_amdgcn_sched_barrier(0);   // the loads issued before this call stay above it
+  const uint32_t l = lane_id();
+  const bool b3 = (l & 8u) != 0, b2 = (l & 4u) != 0;
+  uint64_t h[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int32_t lower = djb2_planes(r.v[2 * i], r.v[2 * i + 1], d, b3);
+    const int32_t upper = djb2_planes(r.v[2 * i + 4], r.v[2 * i + 5], d, b3);
+    h[i] = (uint64_t)(int64_t)deal_sum<kDppXor8>(lower, upper, b3) << (8u * (l & 7u));
+    __builtin_amdgcn_sched_barrier(0);   // two groups' results in registers at a time
+  }
+  return deal_sum<kDppXor7>(h[0], h[1], b2);
+}
+
+// The lane that a sector's sum ends in, for sector s of a tile whose sixteens
+// were dealt over bits 0 and 1 (16p + 4g + k: p's upper bit in 0, lower in 1).
+__device__ __forceinline__ uint32_t djb2_lane_of(uint32_t s) {
+  const uint32_t p = s >> 4, g = (s >> 2) & 3u, k = s & 3u;
+  return 16u * k + 4u * g + ((p & 1u) << 1) + (p >> 1);
 }
 
 // Signature of every sector of a tile (lane l = sector l). A and B are the
 // two register buffers of the load pipeline: on entry A holds (or is
-// receiving) phase 0; phase p+1 loads are issued before phase p is hashed,
-// and `prefetch` (called before the last phase is hashed) may start the next
-// tile's phase 0 into A.
+// receiving) sectors 0-15; the next sixteen are requested before these are
+// hashed, and `prefetch` (called before the last are hashed) may start the
+// next tile's first into A.
 template <bool kNonTemporal, class Rows, class Prefetch>
-__device__ __forceinline__ uint64_t tile_signature_pipelined(const Rows& rows, uint8_t* lds, uint64_t wt,
-                                                             PhaseRegs& A, PhaseRegs& B, Prefetch&& prefetch) {
-  uint32_t acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0;
-  load_phase<kNonTemporal>(rows, 1, B);
-  hash_phase<0>(A, lds, wt, acc);
-  load_phase<kNonTemporal>(rows, 2, A);
-  hash_phase<1>(B, lds, wt, acc);
-  load_phase<kNonTemporal>(rows, 3, B);
-  hash_phase<2>(A, lds, wt, acc);
+__device__ __forceinline__ uint64_t tile_djb2_pipelined(const Rows& rows, const Djb2Lane& d, PhaseRegs& A,
+                                                        PhaseRegs& B, Prefetch&& prefetch) {
+  uint64_t h[4];
+  load_sectors<kNonTemporal>(rows, 1, B);
+  h[0] = djb2_phase(A, d);
+  load_sectors<kNonTemporal>(rows, 2, A);
+  h[1] = djb2_phase(B, d);
+  load_sectors<kNonTemporal>(rows, 3, B);
+  h[2] = djb2_phase(A, d);
   prefetch(A);
-  hash_phase<3>(B, lds, wt, acc);
-  return finish_signature(acc);
+  h[3] = djb2_phase(B, d);
+  const uint32_t l = lane_id();
+  const bool b0 = (l & 1u) != 0, b1 = (l & 2u) != 0;
+  const uint64_t x = deal_sum<kDppXor1>(h[0], h[2], b0), y = deal_sum<kDppXor1>(h[1], h[3], b0);
+  return shfl_u64(deal_sum<kDppXor2>(x, y, b1), djb2_lane_of(l)) + kDjb2Constant;
+}
+
+// Signatures of sixteen sectors held in r (lane l: sector l mod 16).
+__device__ __forceinline__ uint64_t sixteen_djb2(const PhaseRegs& r, const Djb2Lane& d) {
+  uint64_t h = djb2_phase(r, d);
+  h += dpp<kDppXor1>(h);
+  h += dpp<kDppXor2>(h);
+  const uint32_t l = lane_id();
+  return shfl_u64(h, 16u * (l & 3u) + (l & 12u)) + kDjb2Constant;
 }
 
 // ---------------------------------------------------------------- CRC-64
@@ -345,26 +417,35 @@ __device__ __forceinline__ uint32_t bucket_of(uint64_t h, uint32_t log2_buckets)
 // Slot of key h (h != kEmptyKey) or -1. Linear probing over buckets: a key
 // lives in its home bucket or, if that bucket filled up first, a later one
 // (Eq. (3) at bucket granularity); a bucket with a free slot ends the search.
-// The whole 128-byte bucket is loaded before any key is compared: one memory
-// round trip per bucket (keys are distinct, so at most one slot matches).
+// A bucket is read as two 64-byte halves in turn: k_insert claims a bucket's
+// slots in order (and nothing is ever removed), so the occupied slots are a
+// prefix of it and a free slot in the first half ends the search there (about
+// 91% of the buckets of a fragment index, half of a sector index's at its
+// fullest). A whole bucket at once costs 16 more registers, which the scans
+// would spill.
 __device__ __forceinline__ int64_t find_slot(const IndexView& ix, uint64_t h) {
+  constexpr uint32_t kHalf = kBucketSlots / 2;
   const uint32_t nb_mask = (1u << ix.log2_buckets) - 1u;
   uint32_t b = bucket_of(h, ix.log2_buckets);
   for (uint32_t it = 0; it <= nb_mask; ++it) {
-    const u64x2* p = (const u64x2*)(ix.keys + (uint64_t)b * kBucketSlots);
-    u64x2 kv[kBucketSlots / 2];
 #pragma unroll
-    for (int c = 0; c < (int)(kBucketSlots / 2); ++c) kv[c] = p[c];
-    int64_t found = -1;
-    bool any_empty = false;
+    for (uint32_t half = 0; half < 2; ++half) {
+      const uint64_t first = (uint64_t)b * kBucketSlots + half * kHalf;
+      const u64x2* p = (const u64x2*)(ix.keys + first);
+      u64x2 kv[kHalf / 2];
 #pragma unroll
-    for (int c = 0; c < (int)(kBucketSlots / 2); ++c) {
-      if (kv[c].x == h) found = (int64_t)b * kBucketSlots + 2 * c;
-      if (kv[c].y == h) found = (int64_t)b * kBucketSlots + 2 * c + 1;
-      any_empty |= (kv[c].x == kEmptyKey) | (kv[c].y == kEmptyKey);
+      for (int c = 0; c < (int)(kHalf / 2); ++c) kv[c] = p[c];
+      int64_t found = -1;
+      bool any_empty = false;
+#pragma unroll
+      for (int c = 0; c < (int)(kHalf / 2); ++c) {
+        if (kv[c].x == h) found = (int64_t)(first + 2 * c);
+        if (kv[c].y == h) found = (int64_t)(first + 2 * c + 1);
+        any_empty |= (kv[c].x == kEmptyKey) | (kv[c].y == kEmptyKey);
+      }
+      if (found >= 0) return found;
+      if (any_empty) return -1;
     }
-    if (found >= 0) return found;
-    if (any_empty) return -1;
     b = (b + 1) & nb_mask;
   }
   return -1;
@@ -424,18 +505,23 @@ __device__ __forceinline__ bool tau_ok(uint32_t mask, uint32_t tau, bool any_tau
 // is one.
 // bloom / log2_bloom: the filter to consult (the index's, or one position's
 // slice of it), or null. kSlots = false records no slots (slot_out unused),
-// for scans whose flags are not confirmed afterwards.
-template <int kLayout = kLayoutBucketed, uint32_t kSlotStride = 1, bool kSlots = true>
+// for scans whose flags are not confirmed afterwards. kFiltered: there always
+// is a filter (the cooperative probe's registers are not needed). kSectors: 64,
+// or 16 with lane l holding sector l mod 16 (all four lanes of a sector write
+// the same slot, and the mask's bits 16 and above repeat).
+template <int kLayout = kLayoutBucketed, uint32_t kSlotStride = 1, bool kSlots = true, bool kFiltered = false,
+          uint32_t kSectors = kTileSectors>
 __device__ __forceinline__ uint64_t tile_probe(const IndexView& ix, uint64_t h, uint32_t tau, bool any_tau,
                                                uint32_t* __restrict__ slot_out, const uint64_t* bloom,
                                                uint32_t log2_bloom) {
   const uint32_t l = lane_id();
+  const uint32_t own = l % kSectors;   // this lane's sector
   // signature 0 cannot be stored in the table (it marks free slots)
   const bool ok_zero = (h == kEmptyKey) && tau_ok(ix.zero_sig_mask, tau, any_tau);
-  if (kSlots && ok_zero) slot_out[l * kSlotStride] = ix.zero_slot;
-  if (kLayout != kLayoutBucketed || bloom) {
+  if (kSlots && ok_zero) slot_out[own * kSlotStride] = ix.zero_slot;
+  if (kLayout != kLayoutBucketed || kFiltered || bloom) {
     bool maybe = h != kEmptyKey;
-    if (bloom) {
+    if (kFiltered || bloom) {
       uint32_t w;
       uint64_t bits;
       bloom_place(h, log2_bloom, &w, &bits);
@@ -445,16 +531,17 @@ __device__ __forceinline__ uint64_t tile_probe(const IndexView& ix, uint64_t h, 
     if (maybe) {
       const int64_t slot = find_slot_in<kLayout>(ix, h);
       ok = slot >= 0 && tau_ok(ix.tau_mask[slot], tau, any_tau);
-      if (kSlots && ok) slot_out[l * kSlotStride] = (uint32_t)slot;
+      if (kSlots && ok) slot_out[own * kSlotStride] = (uint32_t)slot;
     }
     return ballot(ok) | ballot(ok_zero);
   }
   const uint32_t bkt = bucket_of(h, ix.log2_buckets);
   // per round: the bucket's slots 2(l%8), 2(l%8)+1 and their masks
-  u64x2 kv[8];
-  uint32_t mk[8];
+  constexpr int kRounds = (int)kSectors / 8;
+  u64x2 kv[kRounds];
+  uint32_t mk[kRounds];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = 0; r < kRounds; ++r) {
     const uint32_t s = 8u * r + (l >> 3);
     const uint32_t slot0 = (uint32_t)__shfl((int)bkt, (int)s, kWave) * kBucketSlots + 2u * (l & 7u);
     kv[r] = *(const u64x2*)(ix.keys + slot0);
@@ -462,7 +549,7 @@ __device__ __forceinline__ uint64_t tile_probe(const IndexView& ix, uint64_t h, 
   }
   uint64_t hits = 0, unresolved = 0;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = 0; r < kRounds; ++r) {
     // the round's sector, fetched again rather than kept live across the loads
     const uint32_t s = 8u * r + (l >> 3);
     const uint64_t hs = shfl_u64(h, s);
@@ -481,10 +568,10 @@ __device__ __forceinline__ uint64_t tile_probe(const IndexView& ix, uint64_t h, 
   }
   // rare: the home bucket was full and did not hold the key
   bool ok_more = false;
-  if ((unresolved >> l) & 1u) {
+  if ((unresolved >> own) & 1u) {
     const int64_t slot = find_slot(ix, h);
     ok_more = slot >= 0 && tau_ok(ix.tau_mask[slot], tau, any_tau);
-    if (kSlots && ok_more) slot_out[l * kSlotStride] = (uint32_t)slot;
+    if (kSlots && ok_more) slot_out[own * kSlotStride] = (uint32_t)slot;
   }
   return hits | ballot(ok_more) | ballot(ok_zero);
 }

@@ -156,39 +156,6 @@ struct FragmentWindows {
   __device__ __forceinline__ uint32_t image_between(uint64_t, uint32_t, uint32_t) const { return 0; }
 };
 
-// find_slot reading each bucket as two 64-byte halves in turn. k_insert
-// claims a bucket's slots in order (and nothing is ever removed), so the
-// occupied slots of a bucket are a prefix of it: a free slot in the first
-// half ends the search there. At load 1/2 or less most probes read one half
-// (a fragment index: about 91% of buckets hold at most 8 keys).
-__device__ __forceinline__ int64_t find_slot_halves(const IndexView& ix, uint64_t h) {
-  constexpr uint32_t kHalf = kBucketSlots / 2;
-  const uint32_t nb_mask = (1u << ix.log2_buckets) - 1u;
-  uint32_t b = bucket_of(h, ix.log2_buckets);
-  for (uint32_t it = 0; it <= nb_mask; ++it) {
-#pragma unroll
-    for (uint32_t half = 0; half < 2; ++half) {
-      const uint64_t first = (uint64_t)b * kBucketSlots + half * kHalf;
-      const u64x2* p = (const u64x2*)(ix.keys + first);
-      u64x2 kv[kHalf / 2];
-#pragma unroll
-      for (int c = 0; c < (int)(kHalf / 2); ++c) kv[c] = p[c];
-      int64_t found = -1;
-      bool any_empty = false;
-#pragma unroll
-      for (int c = 0; c < (int)(kHalf / 2); ++c) {
-        if (kv[c].x == h) found = (int64_t)(first + 2 * c);
-        if (kv[c].y == h) found = (int64_t)(first + 2 * c + 1);
-        any_empty |= (kv[c].x == kEmptyKey) | (kv[c].y == kEmptyKey);
-      }
-      if (found >= 0) return found;
-      if (any_empty) return -1;
-    }
-    b = (b + 1) & nb_mask;
-  }
-  return -1;
-}
-
 // A task's image words for lane l: its 16 own dwords (dwords 16l..16l+15 of
 // the task) and, in lanes 0-15, dword 1024 + (l mod 16) (the next task's first
 // words, which lane 63's windows reach). Every task but the image's last lies
@@ -323,7 +290,7 @@ __device__ __forceinline__ void frag_task(uint64_t n_windows, uint64_t n_words, 
         if (sig == kEmptyKey) {
           if (ix.zero_sig_mask) slot = ix.zero_slot;
         } else {
-          slot = find_slot_halves(ix, sig);   // any position: every occupied slot has masters
+          slot = find_slot(ix, sig);   // any position: every occupied slot has masters
         }
         if (slot >= 0) {
           mask |= 1u << w;

@@ -50,6 +50,7 @@ struct OneImage {
   static constexpr bool kManyImages = false;
   ImageDesc d;
   __device__ __forceinline__ uint64_t n_tiles() const { return (d.n_sectors + kTileSectors - 1) / kTileSectors; }
+  __device__ __forceinline__ TileRef tile_at(uint64_t g) const { return tile_of(d, g, 0); }
   // `cursor` is the image of the previous lookup (tiles are visited in increasing order)
   __device__ __forceinline__ TileRef tile(uint64_t g, uint32_t&) const { return tile_of(d, g, 0); }
   __device__ __forceinline__ const ImageDesc& image(uint32_t) const { return d; }
@@ -64,6 +65,10 @@ struct ManyImages {
   const ImageDesc* __restrict__ d;
   uint32_t n;
   __device__ __forceinline__ uint64_t n_tiles() const { return d[n].tile_begin; }
+  __device__ __forceinline__ TileRef tile_at(uint64_t g) const {
+    const uint32_t i = image_of_tile(g);
+    return tile_of(d[i], g, i);
+  }
   __device__ __forceinline__ TileRef tile(uint64_t g, uint32_t& cursor) const {
     // The image holding tile g is the last i with d[i].tile_begin <= g
     // (empty images are skipped). A wave's tiles are a stride of the grid
@@ -102,19 +107,52 @@ struct ManyImages {
   }
 };
 
+// ------------------------------------------------------------ tile hashing
+// What a wave keeps for hashing its tiles with one signature kind: the
+// matrix operands of djb2, or the CRC's staging area in LDS.
+template <int kSig>
+struct TileHash {
+  Djb2Lane d;
+  __device__ __forceinline__ explicit TileHash(uint32_t) { load_djb2_lane(d); }
+  template <class Rows>
+  __device__ __forceinline__ void load(const Rows& rows, PhaseRegs& r) const {   // a tile's first phase
+    load_sectors<true>(rows, 0, r);
+  }
+  template <class Rows, class Prefetch>
+  __device__ __forceinline__ uint64_t tile(const Rows& rows, PhaseRegs& A, PhaseRegs& B, Prefetch&& prefetch) const {
+    return tile_djb2_pipelined<true>(rows, d, A, B, prefetch);
+  }
+};
+template <>
+struct TileHash<kSigCrc64> {
+  uint8_t* my;   // this wave's staging area
+  __device__ __forceinline__ explicit TileHash(uint32_t wave) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kScanWaves * kTileLds];
+    my = lds + wave * kTileLds;
+  }
+  template <class Rows>
+  __device__ __forceinline__ void load(const Rows& rows, PhaseRegs& r) const {
+    load_phase<true>(rows, 0, r);
+  }
+  template <class Rows, class Prefetch>
+  __device__ __forceinline__ uint64_t tile(const Rows& rows, PhaseRegs& A, PhaseRegs& B, Prefetch&& prefetch) const {
+    return tile_crc_pipelined<true>(rows, my, A, B, prefetch);
+  }
+};
+
 // ------------------------------------------------------------------ scan
-// Persistent grid over the tile space: wave q takes chunks q, q + W, ... of
+// Persistent grid over the tile space (the CRC, and djb2 with a launch shape
+// that caps the grid or asks for runs of tiles): wave q takes chunks q, q + W, ... of
 // `chunk` consecutive tiles (W = waves in the grid). 4 waves per SIMD (at
 // most 128 VGPRs): the more waves, the more sector loads in flight per CU.
-// kSig: kSigDjb2 (wt = the digit-plane weight table) or kSigCrc64 (no table;
-// wt unused). kLayout: the index's probe layout (kFlags only).
+// kLayout: the index's probe layout (kFlags only).
 template <int kMode, int kSig, class Src, int kLayout = kLayoutBucketed>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
-    Src src, uint32_t chunk, IndexView ix, uint64_t wt, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kScanWaves * kTileLds];
-  const uint32_t w = threadIdx.x / kWave;
+    Src src, uint32_t chunk, IndexView ix, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
+  // the wave's index, uniform (so tile addresses stay in scalar registers)
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const uint32_t l = lane_id();
-  uint8_t* my = lds + w * kTileLds;
+  TileHash<kSig> hash(w);
   const uint64_t n_tiles = src.n_tiles();
   const uint64_t n_waves = (uint64_t)gridDim.x * kScanWaves;
   uint64_t g = ((uint64_t)blockIdx.x * kScanWaves + w) * chunk;
@@ -125,7 +163,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
   uint32_t cur = 0;
   TileRef tr = src.tile(g, cur);
   PhaseRegs A, B;
-  load_phase<true>(ContiguousRows{tr.base, tr.n_valid}, 0, A);
+  hash.load(ContiguousRows{tr.base, tr.n_valid}, A);
   while (true) {
     const uint64_t gn = next_of(g);
     const bool more = gn < n_tiles;
@@ -139,13 +177,9 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     // loads), which must not hold back this tile's own loads.
     auto prefetch = [&](PhaseRegs& R) {
       if (more) tn = src.tile(gn, cur_n);
-      load_phase<true>(ContiguousRows{tn.base, tn.n_valid}, 0, R);
+      hash.load(ContiguousRows{tn.base, tn.n_valid}, R);
     };
-    uint64_t h;
-    if constexpr (kSig == kSigCrc64)
-      h = tile_crc_pipelined<true>(ContiguousRows{tr.base, tr.n_valid}, my, A, B, prefetch);
-    else
-      h = tile_signature_pipelined<true>(ContiguousRows{tr.base, tr.n_valid}, my, wt, A, B, prefetch);
+    const uint64_t h = hash.tile(ContiguousRows{tr.base, tr.n_valid}, A, B, prefetch);
     if constexpr (kMode == kFlags || kMode == kFlagBits) {
       const uint32_t tau = (tr.tau_first + l) & (kClusterSectors - 1);
       uint64_t hits = tile_probe<kLayout, 1, kMode == kFlags>(
@@ -163,6 +197,71 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
   }
 }
 
+// ------------------------------------------------- djb2, a wave per sixteen sectors
+// The default djb2 scan: a block is one wave, which requests its 16 sectors (8
+// KiB) at once, hashes them on the matrix cores, looks them up and writes their
+// 16 bits of the tile's hit word. No loop and no pipeline in the wave: at about
+// 60 registers eight waves fit a SIMD, 64 KiB of loads in flight on each, and
+// the hardware hands out the next block as a wave ends, so nothing is idle
+// before the last few microseconds. Against the persistent grid of tiles of 64
+// sectors (k_scan, with the same hashing): 1 MiB 6.2 -> 5.1 us, 64 MiB 16.3 ->
+// 13.2, 700 MiB 122 -> 110, 8 GiB 1308 -> 1257 (1253 at that grid's best
+// shape), 6.8 TB/s and bound by HBM. Blocks of four waves were 0-2% slower, 32
+// sectors a wave 1% faster on 8 GiB and up to 7% slower below 1 GiB.
+constexpr uint32_t kPart = 16;                          // sectors per wave
+constexpr uint32_t kTileParts = kTileSectors / kPart;
+constexpr uint64_t kMaxPartBlocks = 1ull << 26;         // a grid has fewer than 2^32 threads
+
+// A wave's sectors `rows` (part `part` of the tile with hit word *out).
+template <int kLayout, uint32_t kSlotStride, bool kSlots, bool kFiltered, class Rows>
+__device__ __forceinline__ void scan_part(const Rows& rows, uint32_t part, uint32_t tau, bool any_tau,
+                                          const IndexView& ix, const uint64_t* bloom, uint32_t log2_bloom,
+                                          uint64_t* out, uint32_t* slots) {
+  uint16_t* bits = (uint16_t*)out + part;   // little-endian: its bits of the word
+  if (rows.n_valid == 0) {                  // past the image's end
+    if (lane_id() == 0) *bits = 0;
+    return;
+  }
+  PhaseRegs r;
+  load_sectors<true>(rows, 0, r);
+  Djb2Lane d;
+  load_djb2_lane(d);
+  const uint64_t h = sixteen_djb2(r, d);
+  const uint64_t hits = tile_probe<kLayout, kSlotStride, kSlots, kFiltered, kPart>(ix, h, tau, any_tau, slots, bloom,
+                                                                                   log2_bloom);
+  if (lane_id() == 0) *bits = (uint16_t)(hits & ((1u << rows.n_valid) - 1u));
+}
+// Sectors of a part that starts `first` sectors into a tile of n.
+__device__ __forceinline__ uint32_t part_valid(uint64_t n, uint64_t first) {
+  return n <= first ? 0u : (n - first < kPart ? (uint32_t)(n - first) : kPart);
+}
+
+// Block b takes part b mod 4 of tile b / 4.
+template <int kMode, class Src, int kLayout>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void k_scan_parts(
+    Src src, IndexView ix, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
+  const uint32_t l = lane_id();
+  const uint32_t part = blockIdx.x % kTileParts, first = part * kPart;
+  const uint64_t g = blockIdx.x / kTileParts;
+  const TileRef tr = src.tile_at(g);
+  const ContiguousRows rows{tr.base + first * kSectorBytes, part_valid(tr.n_valid, first)};
+  if constexpr (kMode == kSigs) {
+    if (rows.n_valid == 0) return;
+    PhaseRegs r;
+    load_sectors<true>(rows, 0, r);
+    Djb2Lane d;
+    load_djb2_lane(d);
+    const uint64_t h = sixteen_djb2(r, d);
+    if (l < rows.n_valid) out[g * kTileSectors + first + l] = h;   // one image: tile g holds sectors 64g..
+  } else {
+    scan_part<kLayout, 1, kMode == kFlags, false>(
+        rows, part, (tr.tau_first + l) & (kClusterSectors - 1), tr.any_tau != 0, ix, ix.bloom, ix.log2_bloom_words,
+        out + g, kMode == kFlags ? hit_slot + g * kTileSectors + first : nullptr);
+  }
+}
+
+// ------------------------------------------------- position-split scan
+// ------------------------------------------------- position-split scan
 // ------------------------------------------------- position-split scan
 // One image, per-cluster rule, split by cluster position. Workgroups are
 // dispatched to the chip's 8 XCDs in turn (block b runs on XCD b mod 8), so
@@ -227,17 +326,16 @@ __device__ __forceinline__ uint64_t tau_claim_read(uint32_t v) {   // lane 0's v
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// kSlots = false: no slot records (hit_slot unused).
+// kSlots = false: no slot records (hit_slot unused). The index has the split filter.
 template <int kSig, int kLayout = kLayoutBucketed, bool kSlots = true>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan_tau(
     const uint8_t* __restrict__ image, uint64_t n_sectors, uint32_t tau0, uint64_t words_per_pos, uint32_t chunk,
-    IndexView ix, uint64_t wt, uint64_t* __restrict__ tau_words, uint32_t* __restrict__ hit_slot,
+    IndexView ix, uint64_t* __restrict__ tau_words, uint32_t* __restrict__ hit_slot,
     unsigned int* __restrict__ ctr) {
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kScanWaves * kTileLds];
   // the wave's index, uniform (so tile addresses stay in scalar registers)
   const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const uint32_t l = lane_id();
-  uint8_t* my = lds + w * kTileLds;
+  TileHash<kSig> hash(w);
   const uint64_t n_waves = (uint64_t)(gridDim.x / kPositions) * kScanWaves;   // per position
   const uint64_t q = (uint64_t)(blockIdx.x / kPositions) * kScanWaves + w;
   auto rows_of = [&](const TauPos& t, uint64_t k) {
@@ -268,7 +366,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
   if (!fixed && !claim_from(cur, tau_claim_read(tau_claim_issue(ctr, cur.p, l)), g, end)) return;
   ClusterStrideRows tr = rows_of(cur, g);
   PhaseRegs A, B;
-  load_phase<true>(tr, 0, A);
+  hash.load(tr, A);
   while (true) {
     // the next tile: the rest of this run, else the wave's next fixed run,
     // else a claim issued now and read when the next tile's first loads are due
@@ -292,18 +390,14 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
         more = claim_from(nxt, tau_claim_read(c), gn, end_n);
       }
       if (more) tn = rows_of(nxt, gn);
-      load_phase<true>(tn, 0, R);
+      hash.load(tn, R);
     };
-    uint64_t h;
-    if constexpr (kSig == kSigCrc64)
-      h = tile_crc_pipelined<true>(tr, my, A, B, prefetch);
-    else
-      h = tile_signature_pipelined<true>(tr, my, wt, A, B, prefetch);
+    const uint64_t h = hash.tile(tr, A, B, prefetch);
     // this position's slice of the filter
-    const uint64_t* bloom = ix.bloom_tau ? ix.bloom_tau + ((uint64_t)cur.p << ix.log2_bloom_tau) : ix.bloom;
-    const uint32_t log2_bloom = ix.bloom_tau ? ix.log2_bloom_tau : ix.log2_bloom_words;
-    uint64_t hits = tile_probe<kLayout, kPositions, kSlots>(
-        ix, h, cur.p, false, kSlots ? hit_slot + (g * kTileSectors * kPositions + cur.r) : nullptr, bloom, log2_bloom);
+    const uint64_t* bloom = ix.bloom_tau + ((uint64_t)cur.p << ix.log2_bloom_tau);
+    uint64_t hits = tile_probe<kLayout, kPositions, kSlots, true>(
+        ix, h, cur.p, false, kSlots ? hit_slot + (g * kTileSectors * kPositions + cur.r) : nullptr, bloom,
+        ix.log2_bloom_tau);
     if (tr.n_valid < kTileSectors) hits &= (1ull << tr.n_valid) - 1ull;
     if (l == 0) tau_words[cur.p * words_per_pos + g] = hits;
     if (!more) break;
@@ -314,6 +408,29 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     end = end_n;
     tr = tn;
   }
+}
+
+
+// The same split for k_scan_parts' way of scanning: block b takes, of position
+// p = b mod 8 (so on XCD p), part (b / 8) mod 4 of tile b / 32. The hardware's
+// hand-out of blocks balances each XCD's waves, so there are no claims: 2651 us
+// against 2722 (2630 at its best launch shape) for k_scan_tau on 16 GiB and 16 M
+// masters, 171 against 199 on 1 GiB. Every word of tau_words is written, the
+// tiles past a position's sectors with zeros.
+template <int kLayout, bool kSlots>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void k_scan_tau_parts(
+    const uint8_t* __restrict__ image, uint64_t n_sectors, uint32_t tau0, uint64_t words_per_pos, IndexView ix,
+    uint64_t* __restrict__ tau_words, uint32_t* __restrict__ hit_slot) {
+  const uint32_t p = blockIdx.x % kPositions, r = (p - tau0) & (kPositions - 1);
+  const uint32_t part = blockIdx.x / kPositions % kTileParts;
+  const uint64_t g = blockIdx.x / (kPositions * kTileParts);
+  const uint64_t k0 = g * kTileSectors + part * kPart;   // its first cluster
+  const ClusterStrideRows rows{image + (k0 * kPositions + r) * kSectorBytes,
+                               part_valid(position_count(n_sectors, r), k0)};
+  scan_part<kLayout, kPositions, kSlots, true>(rows, part, p, false, ix,
+                                               ix.bloom_tau + ((uint64_t)p << ix.log2_bloom_tau), ix.log2_bloom_tau,
+                                               tau_words + p * words_per_pos + g,
+                                               kSlots ? hit_slot + (k0 * kPositions + r) : nullptr);
 }
 
 }  // namespace carve

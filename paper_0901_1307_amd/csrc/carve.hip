@@ -21,9 +21,9 @@
 //   k_confirm_emit    ordered match records, at offsets it adds up itself
 //   k_stage_out       (server) counts, ids and records into pinned host memory
 // Index build (Section 3.1, Eq. (3)):
-//   k_master_meta, k_scan<kSigs> / k_frag_sigs, k_insert, k_narrow_masks,
-//   k_scatter, k_sort_segments, k_bloom_build; k_occupied, k_insert_linear and
-//   a radix sort for the other layouts; k_lds_filter_build for fragments.
+//   k_master_meta, k_scan_parts<kSigs> / k_frag_sigs, k_insert, k_scatter,
+//   k_sort_segments, k_bloom_build; k_occupied, k_insert_linear and a radix
+//   sort for the other layouts; k_lds_filter_build for fragments.
 #include <hip/hip_runtime.h>
 #include <stdarg.h>
 #include <stdint.h>
@@ -97,10 +97,6 @@ struct Count {
   }
 };
 
-struct U32Items {
-  const uint32_t* v;
-  __device__ __forceinline__ uint64_t operator()(uint64_t i) const { return v[i]; }
-};
 struct PopcountItems {
   const uint64_t* words;
   __device__ __forceinline__ uint64_t operator()(uint64_t i) const { return (uint64_t)__popcll(words[i]); }
@@ -317,16 +313,16 @@ __global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint6
     }
   }
 }
-// u32 counts -> exclusive offsets (out[n] = total).
-template <class T>
+// Counts -> exclusive offsets (out[n] = total).
+template <class Items>
 struct EmitOffsets {
   static constexpr bool kDenseOut = true;   // out[i] for every item i: k_apply stores it coalesced
-  const uint32_t* v;
-  T* out;
-  __device__ __forceinline__ uint64_t load(uint64_t i) const { return v[i]; }
+  Items items;
+  uint32_t* out;
+  __device__ __forceinline__ uint64_t load(uint64_t i) const { return items(i); }
   __device__ __forceinline__ uint64_t count_of(uint64_t x) const { return x; }
-  __device__ __forceinline__ void emit(uint64_t i, uint64_t, uint64_t pos) const { out[i] = (T)pos; }
-  __device__ __forceinline__ void finish(uint64_t n, uint64_t end) const { out[n] = (T)end; }
+  __device__ __forceinline__ void emit(uint64_t i, uint64_t, uint64_t pos) const { out[i] = (uint32_t)pos; }
+  __device__ __forceinline__ void finish(uint64_t n, uint64_t end) const { out[n] = (uint32_t)end; }
 };
 
 // A chunk's items go through LDS: loaded coalesced (consecutive threads,
@@ -458,30 +454,53 @@ __global__ void k_master_meta(const uint64_t* __restrict__ off, uint32_t n_files
 
 // Insert every master signature (Eq. (3) at bucket granularity): first free
 // slot of the home bucket, else of the next bucket, and so on. Equal
-// signatures share one slot. Records the slot of each master, the cluster
-// positions present per slot and the number of masters per slot.
-__global__ void k_insert(const uint64_t* __restrict__ sig, const uint32_t* __restrict__ m_k, uint64_t n_masters,
-                         uint64_t* keys, uint32_t log2_buckets, uint32_t* tau_mask, uint32_t* cnt,
-                         uint32_t* __restrict__ m_slot, uint32_t* overflow, uint32_t* failed) {
+// signatures share one slot. Records the slot of each master and its rank among
+// the slot's (in no particular order): the master that claimed the slot has
+// rank 0, each other one takes the next from extra[slot].
+// Bound by its atomics on scattered words (9 to 20 per ns over the chip), so a
+// master makes one, the claim, unless it is a duplicate; what else a slot needs
+// (its count, its positions) is worked out afterwards. Half a bucket is read at
+// once and compared: slots are claimed in order and keep their key, so the ones
+// before the first that reads as free need no more, and from there on a
+// compare-and-swap decides, normally the first. (1M masters: 116 us, from 163
+// with a count and a position mask kept by atomics and slots tried one by one,
+// and 50 less in the kernels after it.)
+__global__ void k_insert(const uint64_t* __restrict__ sig, uint64_t n_masters, uint64_t* keys, uint32_t log2_buckets,
+                         uint32_t* extra, uint32_t* __restrict__ m_slot, uint32_t* __restrict__ m_rank,
+                         uint32_t* overflow, uint32_t* failed) {
+  constexpr uint32_t kHalf = kBucketSlots / 2;
   const uint64_t m = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_masters) return;
   const uint64_t h = sig[m];
   const uint64_t n_slots = (uint64_t)kBucketSlots << log2_buckets;
   uint64_t slot = n_slots;   // side slot of signature 0
+  bool claimed = false;
   if (h != kEmptyKey) {
     const uint32_t nb_mask = (1u << log2_buckets) - 1u;
     const uint32_t home = bucket_of(h, log2_buckets);
     uint32_t b = home;
     bool placed = false;
     for (uint32_t it = 0; it <= nb_mask && !placed; ++it) {
-      for (uint32_t sl = 0; sl < kBucketSlots; ++sl) {
-        unsigned long long* p = (unsigned long long*)(keys + (uint64_t)b * kBucketSlots + sl);
-        unsigned long long cur = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == kEmptyKey) cur = atomicCAS(p, (unsigned long long)kEmptyKey, (unsigned long long)h);
-        if (cur == kEmptyKey || cur == h) {   // claimed it, or it already holds h
-          slot = (uint64_t)b * kBucketSlots + sl;
+      for (uint32_t half = 0; half < 2 && !placed; ++half) {
+        const uint64_t first = (uint64_t)b * kBucketSlots + half * kHalf;
+        unsigned long long* p = (unsigned long long*)(keys + first);
+        unsigned long long k[kHalf];
+#pragma unroll
+        for (uint32_t i = 0; i < kHalf; ++i) k[i] = __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t at = kHalf, free = kHalf;   // the slot that holds h; the first one seen free
+#pragma unroll
+        for (uint32_t i = kHalf; i-- > 0;) {
+          if (k[i] == h) at = i;
+          if (k[i] == kEmptyKey) free = i;
+        }
+        for (; at == kHalf && free < kHalf; ++free) {
+          const unsigned long long cur = atomicCAS(p + free, (unsigned long long)kEmptyKey, (unsigned long long)h);
+          if (cur == kEmptyKey || cur == h) at = free;   // claimed it, or it already holds h
+          claimed = cur == kEmptyKey;
+        }
+        if (at < kHalf) {
+          slot = first + at;
           placed = true;
-          break;
         }
       }
       if (!placed) b = (b + 1) & nb_mask;
@@ -494,22 +513,19 @@ __global__ void k_insert(const uint64_t* __restrict__ sig, const uint32_t* __res
     if (b != home) atomicAdd(overflow, 1u);
   }
   m_slot[m] = (uint32_t)slot;
-  atomicOr(&tau_mask[slot], 1u << (m_k[m] & (kClusterSectors - 1)));
-  atomicAdd(&cnt[slot], 1u);
+  m_rank[m] = claimed ? 0u : atomicAdd(&extra[slot], 1u) + (slot < n_slots ? 1u : 0u);
 }
 
-// Bloom filter of the table's keys (signature 0 is kept apart and not in it).
-__global__ void k_bloom_build(const uint64_t* __restrict__ keys, uint64_t n_slots, uint32_t log2_words,
-                              uint64_t* bloom) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_slots) return;
-  const uint64_t h = keys[i];
-  if (h == kEmptyKey) return;
-  uint32_t w;
-  uint64_t bits;
-  bloom_place(h, log2_words, &w, &bits);
-  atomicOr((unsigned long long*)(bloom + w), (unsigned long long)bits);
-}
+// Masters per list: a table slot's claimer and its duplicates, or those of
+// signature 0 (list n_slots, which nobody claims).
+struct ListCounts {
+  const uint64_t* keys;
+  const uint32_t* extra;
+  uint64_t n_slots;
+  __device__ __forceinline__ uint64_t operator()(uint64_t i) const {
+    return extra[i] + (i < n_slots && keys[i] != kEmptyKey ? 1u : 0u);
+  }
+};
 
 // The filter split by cluster position: slice t holds the keys with a master
 // at position t (placed like the whole filter, in 2^log2_words words). Built
@@ -522,8 +538,11 @@ __global__ void k_bloom_build(const uint64_t* __restrict__ keys, uint64_t n_slot
 // a launch more where the compaction would take one (about 4 us up to 512 MiB),
 // so it starts above that. carve_scan_config.split overrides it.
 constexpr uint32_t kSplitMinLog2 = 20;
-__global__ void k_bloom_tau_build(const uint64_t* __restrict__ keys, const uint8_t* __restrict__ tau_mask,
-                                  uint64_t n_slots, uint32_t log2_words, uint64_t* bloom_tau) {
+//
+// k_bloom_build: both filters of a sector index from the table's keys
+// (signature 0 is kept apart and in neither), in one pass over the table.
+__global__ void k_bloom_build(const uint64_t* __restrict__ keys, const uint8_t* __restrict__ tau_mask, uint64_t n_slots,
+                              uint32_t log2_words, uint64_t* bloom, uint32_t log2_tau, uint64_t* bloom_tau) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_slots) return;
   const uint64_t h = keys[i];
@@ -531,8 +550,10 @@ __global__ void k_bloom_tau_build(const uint64_t* __restrict__ keys, const uint8
   uint32_t w;
   uint64_t bits;
   bloom_place(h, log2_words, &w, &bits);
+  atomicOr((unsigned long long*)(bloom + w), (unsigned long long)bits);
+  bloom_place(h, log2_tau, &w, &bits);
   for (uint32_t m = tau_mask[i]; m; m &= m - 1u)
-    atomicOr((unsigned long long*)(bloom_tau + ((uint64_t)__builtin_ctz(m) << log2_words) + w),
+    atomicOr((unsigned long long*)(bloom_tau + ((uint64_t)__builtin_ctz(m) << log2_tau) + w),
              (unsigned long long)bits);
 }
 
@@ -597,37 +618,57 @@ __global__ void k_insert_linear(const uint64_t* __restrict__ in_keys, const uint
   }
 }
 
-__global__ void k_narrow_masks(const uint32_t* __restrict__ m32, uint64_t n, uint8_t* __restrict__ m8) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) m8[i] = (uint8_t)m32[i];
-}
-
-__global__ void k_scatter(const uint32_t* __restrict__ m_slot, uint64_t n_masters, const uint32_t* __restrict__ cand_off,
-                          uint32_t* cursor, uint32_t* __restrict__ unsorted) {
+__global__ void k_scatter(const uint32_t* __restrict__ m_slot, const uint32_t* __restrict__ m_rank, uint64_t n_masters,
+                          const uint32_t* __restrict__ cand_off, uint32_t* __restrict__ unsorted) {
   const uint64_t m = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_masters) return;
   const uint32_t s = m_slot[m];
-  if (s == kNoSlot) return;
-  unsorted[cand_off[s] + atomicAdd(&cursor[s], 1u)] = (uint32_t)m;
+  if (s != kNoSlot) unsorted[cand_off[s] + m_rank[m]] = (uint32_t)m;
 }
 
 // Candidate lists in ascending master order (so matches come out ordered by
-// file, then sector in file): one wave per list; each element goes to its
-// rank among the list's (distinct) elements, from `unsorted` into `cand`.
+// file, then sector in file): each element goes to its rank among the list's
+// (distinct) elements, from `unsorted` into `cand`, and the positions present in
+// a list make its mask. A thread per list, since
+// nearly all hold none or one; the lists of more than kThreadList are left to
+// the whole wave, one after another. (A wave per list took 188 us for the 2M
+// slots of 1M masters, this 14.)
+constexpr uint32_t kThreadList = 8;
 __global__ __launch_bounds__(kBlockThreads) void k_sort_segments(const uint32_t* __restrict__ cand_off, uint64_t n_lists,
                                                                 const uint32_t* __restrict__ unsorted,
-                                                                uint32_t* __restrict__ cand) {
+                                                                const uint32_t* __restrict__ m_k,
+                                                                uint32_t* __restrict__ cand,
+                                                                uint8_t* __restrict__ tau_mask) {
   const uint32_t l = lane_id();
-  const uint64_t waves = (uint64_t)gridDim.x * (kBlockThreads / kWave);
-  for (uint64_t s = (uint64_t)blockIdx.x * (kBlockThreads / kWave) + threadIdx.x / kWave; s < n_lists; s += waves) {
-    const uint32_t a = cand_off[s], e = cand_off[s + 1];
-    for (uint32_t i = a + l; i < e; i += kWave) {
+  const uint64_t s = (uint64_t)blockIdx.x * kBlockThreads + threadIdx.x;
+  const uint32_t a = s < n_lists ? cand_off[s] : 0u, e = s < n_lists ? cand_off[s + 1] : 0u;
+  const bool mine = e - a <= kThreadList;
+  uint32_t mask = 0;
+  for (uint32_t i = a; mine && i < e; ++i) {
+    const uint32_t v = unsorted[i];
+    uint32_t rank = 0;
+    for (uint32_t j = a; j < e; ++j) rank += unsorted[j] < v;
+    cand[a + rank] = v;
+    mask |= 1u << (m_k[v] & (kClusterSectors - 1));
+  }
+  for (uint64_t left = ballot(!mine); left; left &= left - 1) {
+    const int from = __ffsll((long long)left) - 1;
+    const uint32_t wa = (uint32_t)__shfl((int)a, from), we = (uint32_t)__shfl((int)e, from);
+    uint32_t part = 0;
+    for (uint32_t i = wa + l; i < we; i += kWave) {
       const uint32_t v = unsorted[i];
       uint32_t rank = 0;
-      for (uint32_t j = a; j < e; ++j) rank += unsorted[j] < v;
-      cand[a + rank] = v;
+      for (uint32_t j = wa; j < we; ++j) rank += unsorted[j] < v;
+      cand[wa + rank] = v;
+      part |= 1u << (m_k[v] & (kClusterSectors - 1));
+    }
+#pragma unroll
+    for (uint32_t b = 0; b < kClusterSectors; ++b) {   // the lanes' positions together, kept by the list's lane
+      const bool present = ballot((part >> b) & 1u) != 0;
+      if (l == (uint32_t)from) mask |= (present ? 1u : 0u) << b;
     }
   }
+  if (s < n_lists) tau_mask[s] = (uint8_t)mask;
 }
 
 // -------------------------------------------------------- confirmation
@@ -1032,17 +1073,17 @@ int resident_grid(Kernel kernel, int threads, uint64_t want, uint32_t per_cu_cap
   return (int)(want < cap ? (want ? want : 1) : cap);
 }
 
-// Exclusive scan of n u32 counts into out[0..n] (out[n] = total); total also
-// left in *d_total. ws holds the block sums and offsets.
-template <class T>
-int scan_counts(const uint32_t* in, T* out, uint64_t n, uint64_t* d_total, DevBuf& ws, hipStream_t s) {
+// Exclusive scan of n counts into out[0..n] (out[n] = total); total also left in
+// *d_total. ws holds the block sums and offsets.
+template <class Items>
+int scan_counts(const Items& items, uint32_t* out, uint64_t n, uint64_t* d_total, DevBuf& ws, hipStream_t s) {
   const uint64_t nb = cdiv(n ? n : 1, kItemsPerBlock);
   CARVE_TRY(ws.reserve(2 * nb * sizeof(uint64_t)));
   uint64_t* sums = ws.as<uint64_t>();
   uint64_t* offs = sums + nb;
-  k_reduce<<<nb, kBlockThreads, 0, s>>>(U32Items{in}, Count{n, nullptr}, sums);
+  k_reduce<<<nb, kBlockThreads, 0, s>>>(items, Count{n, nullptr}, sums);
   k_scan_blocks<<<1, kBlockThreads, 0, s>>>(sums, Count{n, nullptr}, offs, d_total);
-  k_apply<<<nb, kBlockThreads, 0, s>>>(EmitOffsets<T>{in, out}, Count{n, nullptr}, offs);   // also out[n]
+  k_apply<<<nb, kBlockThreads, 0, s>>>(EmitOffsets<Items>{items, out}, Count{n, nullptr}, offs);   // also out[n]
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }
@@ -1771,13 +1812,13 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
       (rc = ix->cand_off.reserve((n_lists + 1) * 4)) || (rc = ix->cand.reserve((n_masters ? n_masters : 1) * 4)) ||
       (rc = ix->m_file.reserve((n_masters ? n_masters : 1) * 4)) || (rc = ix->m_k.reserve((n_masters ? n_masters : 1) * 4)))
     return bail(rc);
-  DevBuf d_off, sig, cnt, m_slot, tmp, ws, misc, mask32;
+  DevBuf d_off, sig, extra, m_slot, m_rank, tmp, ws, misc;
   auto cleanup = [&]() {
-    mask32.release();
     d_off.release();
     sig.release();
-    cnt.release();
+    extra.release();
     m_slot.release();
+    m_rank.release();
     tmp.release();
     ws.release();
     misc.release();
@@ -1787,9 +1828,9 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     return bail(code);
   };
   if ((rc = d_off.reserve((n_files + 1) * 8)) || (rc = sig.reserve((n_masters ? n_masters : 1) * 8)) ||
-      (rc = cnt.reserve(n_lists * 4)) || (rc = m_slot.reserve((n_masters ? n_masters : 1) * 4)) ||
-      (rc = tmp.reserve((n_masters ? n_masters : 1) * 4)) || (rc = misc.reserve(64)) ||
-      (rc = mask32.reserve(n_lists * 4)))
+      (rc = extra.reserve(n_lists * 4)) || (rc = m_slot.reserve((n_masters ? n_masters : 1) * 4)) ||
+      (rc = m_rank.reserve((n_masters ? n_masters : 1) * 4)) ||
+      (rc = tmp.reserve((n_masters ? n_masters : 1) * 4)) || (rc = misc.reserve(64)))
     return bail2(rc);
   uint32_t* d_overflow = misc.as<uint32_t>();
   uint32_t* d_failed = d_overflow + 1;
@@ -1800,8 +1841,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     if (e_ != hipSuccess) return bail2(fail(CARVE_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_))); \
   } while (0)
   BUILD_TRY(hipMemsetAsync(ix->keys.p, 0, ix->n_slots * 8, s));
-  BUILD_TRY(hipMemsetAsync(mask32.p, 0, n_lists * 4, s));
-  BUILD_TRY(hipMemsetAsync(cnt.p, 0, n_lists * 4, s));
+  BUILD_TRY(hipMemsetAsync(extra.p, 0, n_lists * 4, s));
   BUILD_TRY(hipMemsetAsync(misc.p, 0, 64, s));
   if (n_masters) {
     BUILD_TRY(hipMemcpyAsync(d_off.p, file_sector_offsets, (n_files + 1) * 8, hipMemcpyHostToDevice, s));
@@ -1817,23 +1857,22 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
                                      nullptr, s)))
         return bail2(rc);
     }
-    k_insert<<<nbk, 256, 0, s>>>(sig.as<uint64_t>(), ix->m_k.as<uint32_t>(), n_masters, ix->keys.as<uint64_t>(), lb,
-                                mask32.as<uint32_t>(), cnt.as<uint32_t>(), m_slot.as<uint32_t>(), d_overflow,
-                                d_failed);
+    k_insert<<<nbk, 256, 0, s>>>(sig.as<uint64_t>(), n_masters, ix->keys.as<uint64_t>(), lb, extra.as<uint32_t>(),
+                                m_slot.as<uint32_t>(), m_rank.as<uint32_t>(), d_overflow, d_failed);
     BUILD_TRY(hipGetLastError());
   }
-  k_narrow_masks<<<cdiv(n_lists, 256), 256, 0, s>>>(mask32.as<uint32_t>(), n_lists, ix->tau_mask.as<uint8_t>());
-  if ((rc = scan_counts<uint32_t>(cnt.as<uint32_t>(), ix->cand_off.as<uint32_t>(), n_lists, d_total, ws, s)))
+  const ListCounts counts{ix->keys.as<uint64_t>(), extra.as<uint32_t>(), ix->n_slots};
+  if ((rc = scan_counts(counts, ix->cand_off.as<uint32_t>(), n_lists, d_total, ws, s)))
     return bail2(rc);
   if (n_masters) {
-    BUILD_TRY(hipMemsetAsync(cnt.p, 0, n_lists * 4, s));   // reused as scatter cursors
     const uint32_t nbk = (uint32_t)cdiv(n_masters, 256);
-    k_scatter<<<nbk, 256, 0, s>>>(m_slot.as<uint32_t>(), n_masters, ix->cand_off.as<uint32_t>(), cnt.as<uint32_t>(),
+    k_scatter<<<nbk, 256, 0, s>>>(m_slot.as<uint32_t>(), m_rank.as<uint32_t>(), n_masters, ix->cand_off.as<uint32_t>(),
                                  tmp.as<uint32_t>());
-    k_sort_segments<<<device_cus() * 8, kBlockThreads, 0, s>>>(ix->cand_off.as<uint32_t>(), n_lists,
-                                                                tmp.as<uint32_t>(), ix->cand.as<uint32_t>());
-    BUILD_TRY(hipGetLastError());
   }
+  k_sort_segments<<<(unsigned)cdiv(n_lists, kBlockThreads), kBlockThreads, 0, s>>>(
+      ix->cand_off.as<uint32_t>(), n_lists, tmp.as<uint32_t>(), ix->m_k.as<uint32_t>(), ix->cand.as<uint32_t>(),
+      ix->tau_mask.as<uint8_t>());
+  BUILD_TRY(hipGetLastError());
   {   // distinct signatures = non-empty candidate lists
     const uint64_t nb = cdiv(n_lists, kItemsPerBlock);
     if ((rc = ws.reserve(2 * nb * 8))) return bail2(rc);
@@ -1845,10 +1884,10 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
   }
   uint32_t h_misc[2] = {0, 0};
   uint64_t h_unique = 0;
-  uint32_t zmask = 0;
+  uint8_t zmask = 0;
   BUILD_TRY(hipMemcpyAsync(h_misc, misc.p, 8, hipMemcpyDeviceToHost, s));
   BUILD_TRY(hipMemcpyAsync(&h_unique, d_total + 1, 8, hipMemcpyDeviceToHost, s));
-  BUILD_TRY(hipMemcpyAsync(&zmask, mask32.as<uint32_t>() + ix->n_slots, 4, hipMemcpyDeviceToHost, s));
+  BUILD_TRY(hipMemcpyAsync(&zmask, ix->tau_mask.as<uint8_t>() + ix->n_slots, 1, hipMemcpyDeviceToHost, s));
   BUILD_TRY(hipStreamSynchronize(s));
 #undef BUILD_TRY
   if (h_misc[1]) return bail2(fail(CARVE_EDEVICE, "build_master_index: %u keys could not be placed", h_misc[1]));
@@ -1881,9 +1920,6 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
       if (unit == kFragBytes)   // the same bytes as 2^(lw+1) words of 32 bits, 3 bits per signature
         k_frag_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->n_slots, lw + 1,
                                                                    zmask ? 1u : 0u, ix->bloom.as<uint32_t>());
-      else
-        k_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->n_slots, lw,
-                                                            ix->bloom.as<uint64_t>());
       // The filter split by position (sector indexes): slice t holds the keys
       // with a master at position t, about an eighth of them, and each XCD of a
       // position-split scan keeps only its slice in L2, so the slices are sized
@@ -1905,8 +1941,9 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
         ix->log2_bloom_tau = ls;
         if (hipMemsetAsync(ix->bloom_tau.p, 0, (8ull * kPositions) << ls, s) != hipSuccess)
           return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom memset failed"));
-        k_bloom_tau_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->tau_mask.as<uint8_t>(),
-                                                                ix->n_slots, ls, ix->bloom_tau.as<uint64_t>());
+        k_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->tau_mask.as<uint8_t>(),
+                                                            ix->n_slots, lw, ix->bloom.as<uint64_t>(), ls,
+                                                            ix->bloom_tau.as<uint64_t>());
       }
       if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom build failed"));

@@ -30,6 +30,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint6
     }
   }
 }
-// Counts -> exclusive offsets (out[n] = total).
+// Counts -> exclusive offsets (out[n] = total), the low 32 bits of both.
 template <class Items>
 struct EmitOffsets {
   static constexpr bool kDenseOut = true;   // out[i] for every item i: k_apply stores it coalesced
@@ -433,11 +434,6 @@ __global__ void k_clear_counts(uint64_t* count, uint64_t* host) {
   host[0] = host[1] = host[kConfirmedWord] = 0;
 }
 
-struct NonEmptyLists {
-  const uint32_t* off;
-  __device__ __forceinline__ uint64_t operator()(uint64_t i) const { return off[i + 1] != off[i] ? 1u : 0u; }
-};
-
 // ------------------------------------------------------------ build
 __global__ void k_master_meta(const uint64_t* __restrict__ off, uint32_t n_files, uint64_t n_masters,
                               uint32_t* __restrict__ m_file, uint32_t* __restrict__ m_k) {
@@ -517,13 +513,16 @@ __global__ void k_insert(const uint64_t* __restrict__ sig, uint64_t n_masters, u
 }
 
 // Masters per list: a table slot's claimer and its duplicates, or those of
-// signature 0 (list n_slots, which nobody claims).
+// signature 0 (list n_slots, which nobody claims). Bits 32 and up count the list
+// itself when it holds any, so one scan gives the lists' offsets (the low halves
+// of the positions) and, in the total, the number of distinct signatures.
 struct ListCounts {
   const uint64_t* keys;
   const uint32_t* extra;
   uint64_t n_slots;
   __device__ __forceinline__ uint64_t operator()(uint64_t i) const {
-    return extra[i] + (i < n_slots && keys[i] != kEmptyKey ? 1u : 0u);
+    const uint32_t n = extra[i] + (i < n_slots && keys[i] != kEmptyKey ? 1u : 0u);
+    return n ? (1ull << 32) + n : 0;
   }
 };
 
@@ -638,7 +637,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_sort_segments(const uint32_t*
                                                                 const uint32_t* __restrict__ unsorted,
                                                                 const uint32_t* __restrict__ m_k,
                                                                 uint32_t* __restrict__ cand,
-                                                                uint8_t* __restrict__ tau_mask) {
+                                                                uint8_t* __restrict__ tau_mask,
+                                                                uint32_t* __restrict__ last_mask) {
   const uint32_t l = lane_id();
   const uint64_t s = (uint64_t)blockIdx.x * kBlockThreads + threadIdx.x;
   const uint32_t a = s < n_lists ? cand_off[s] : 0u, e = s < n_lists ? cand_off[s + 1] : 0u;
@@ -669,6 +669,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_sort_segments(const uint32_t*
     }
   }
   if (s < n_lists) tau_mask[s] = (uint8_t)mask;
+  if (s == n_lists - 1) *last_mask = mask;   // signature 0's, for the host
 }
 
 // -------------------------------------------------------- confirmation
@@ -970,28 +971,57 @@ int fail(int code, const char* fmt, ...) {
     if (r_ != CARVE_OK) return r_; \
   } while (0)
 
-// Device buffer that grows on demand (contents not preserved).
+// Device buffer that grows on demand (contents not preserved), or a part of
+// another one (carve_up).
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
+  bool part = false;
   int reserve(size_t need) {
     if (need <= bytes) return CARVE_OK;
-    if (p) (void)hipFree(p);
-    p = nullptr;
-    bytes = 0;
+    release();
     size_t sz = need < 256 ? 256 : need;
-    if (hipMalloc(&p, sz) != hipSuccess) return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
+    if (hipMalloc(&p, sz) != hipSuccess) {
+      p = nullptr;
+      return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
+    }
     bytes = sz;
     return CARVE_OK;
   }
   template <class T>
   T* as() const { return (T*)p; }
   void release() {
-    if (p) (void)hipFree(p);
+    if (p && !part) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
+    part = false;
   }
 };
+
+// One allocation for several buffers of known sizes, which become its parts (on
+// 256-byte boundaries). An allocation or a free of some MiB costs 30-300 us of
+// host time, so an index is built with three (what it keeps, its filters, what
+// only the build uses) rather than fifteen: build and first scan of 1M masters
+// 1545 -> 880 us. The parts are released before or after `whole`, no matter.
+struct PartSize {
+  DevBuf* buf;
+  size_t need;
+};
+int carve_up(DevBuf& whole, std::initializer_list<PartSize> parts) {
+  auto size_of = [](const PartSize& q) { return q.need < 256 ? (size_t)256 : q.need; };
+  size_t all = 0;
+  for (const PartSize& q : parts) all += (size_of(q) + 255) / 256 * 256;
+  CARVE_TRY(whole.reserve(all));
+  uint8_t* at = whole.as<uint8_t>();
+  for (const PartSize& q : parts) {
+    q.buf->release();
+    q.buf->p = at;
+    q.buf->bytes = size_of(q);
+    q.buf->part = true;
+    at += (size_of(q) + 255) / 256 * 256;
+  }
+  return CARVE_OK;
+}
 
 // Pinned host buffer that grows on demand.
 struct HostBuf {
@@ -1224,6 +1254,7 @@ struct carve_index {
   uint32_t unit_bytes = kSectorBytes;   // master units: sectors, or 64-byte fragments
   uint32_t log2_bloom_words = 0;
   carve_scan_config cfg{};
+  DevBuf mem, filters;                                         // the allocations behind the parts below
   DevBuf keys, tau_mask, cand_off, cand, m_file, m_k, bloom;   // tau_mask: one byte per slot
   uint32_t layout = CARVE_LAYOUT_BUCKETED;
   DevBuf lin_keys, lin_slot, sorted_keys, sorted_slot;          // probe structures of the other layouts
@@ -1654,6 +1685,8 @@ extern "C" void free_index(carve_index* idx) {
   idx->sorted_slot.release();
   idx->lds_filter.release();
   idx->bloom_tau.release();
+  idx->mem.release();
+  idx->filters.release();
   delete idx;
 }
 
@@ -1808,41 +1841,39 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
   const uint64_t n_lists = ix->n_slots + 1;   // + side slot of signature 0
 
   int rc;
-  if ((rc = ix->keys.reserve(ix->n_slots * 8)) || (rc = ix->tau_mask.reserve(n_lists)) ||
-      (rc = ix->cand_off.reserve((n_lists + 1) * 4)) || (rc = ix->cand.reserve((n_masters ? n_masters : 1) * 4)) ||
-      (rc = ix->m_file.reserve((n_masters ? n_masters : 1) * 4)) || (rc = ix->m_k.reserve((n_masters ? n_masters : 1) * 4)))
+  const size_t per_master = n_masters ? n_masters : 1;
+  if ((rc = carve_up(ix->mem, {{&ix->keys, ix->n_slots * 8},
+                               {&ix->tau_mask, n_lists},
+                               {&ix->cand_off, (n_lists + 1) * 4},
+                               {&ix->cand, per_master * 4},
+                               {&ix->m_file, per_master * 4},
+                               {&ix->m_k, per_master * 4}})))
     return bail(rc);
-  DevBuf d_off, sig, extra, m_slot, m_rank, tmp, ws, misc;
-  auto cleanup = [&]() {
-    d_off.release();
-    sig.release();
-    extra.release();
-    m_slot.release();
-    m_rank.release();
-    tmp.release();
-    ws.release();
-    misc.release();
-  };
+  DevBuf work, d_off, sig, extra, m_slot, m_rank, tmp, ws, misc;
   auto bail2 = [&](int code) {
-    cleanup();
+    work.release();
     return bail(code);
   };
-  if ((rc = d_off.reserve((n_files + 1) * 8)) || (rc = sig.reserve((n_masters ? n_masters : 1) * 8)) ||
-      (rc = extra.reserve(n_lists * 4)) || (rc = m_slot.reserve((n_masters ? n_masters : 1) * 4)) ||
-      (rc = m_rank.reserve((n_masters ? n_masters : 1) * 4)) ||
-      (rc = tmp.reserve((n_masters ? n_masters : 1) * 4)) || (rc = misc.reserve(64)))
+  if ((rc = carve_up(work, {{&d_off, (n_files + 1) * 8ull},
+                            {&sig, per_master * 8},
+                            {&m_slot, per_master * 4},
+                            {&m_rank, per_master * 4},
+                            {&tmp, per_master * 4},
+                            {&ws, 2 * cdiv(n_lists, kItemsPerBlock) * 8},
+                            {&misc, 64},
+                            {&extra, n_lists * 4}})))
     return bail2(rc);
   uint32_t* d_overflow = misc.as<uint32_t>();
   uint32_t* d_failed = d_overflow + 1;
   uint64_t* d_total = misc.as<uint64_t>() + 1;
+  uint32_t* d_zero_mask = (uint32_t*)(d_total + 1);
 #define BUILD_TRY(expr)                                                                            \
   do {                                                                                             \
     hipError_t e_ = (expr);                                                                        \
     if (e_ != hipSuccess) return bail2(fail(CARVE_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_))); \
   } while (0)
   BUILD_TRY(hipMemsetAsync(ix->keys.p, 0, ix->n_slots * 8, s));
-  BUILD_TRY(hipMemsetAsync(extra.p, 0, n_lists * 4, s));
-  BUILD_TRY(hipMemsetAsync(misc.p, 0, 64, s));
+  BUILD_TRY(hipMemsetAsync(misc.p, 0, (size_t)(extra.as<uint8_t>() - misc.as<uint8_t>()) + n_lists * 4, s));
   if (n_masters) {
     BUILD_TRY(hipMemcpyAsync(d_off.p, file_sector_offsets, (n_files + 1) * 8, hipMemcpyHostToDevice, s));
     const uint32_t nbk = (uint32_t)cdiv(n_masters, 256);
@@ -1871,27 +1902,20 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
   }
   k_sort_segments<<<(unsigned)cdiv(n_lists, kBlockThreads), kBlockThreads, 0, s>>>(
       ix->cand_off.as<uint32_t>(), n_lists, tmp.as<uint32_t>(), ix->m_k.as<uint32_t>(), ix->cand.as<uint32_t>(),
-      ix->tau_mask.as<uint8_t>());
+      ix->tau_mask.as<uint8_t>(), d_zero_mask);
   BUILD_TRY(hipGetLastError());
-  {   // distinct signatures = non-empty candidate lists
-    const uint64_t nb = cdiv(n_lists, kItemsPerBlock);
-    if ((rc = ws.reserve(2 * nb * 8))) return bail2(rc);
-    k_reduce<<<nb, kBlockThreads, 0, s>>>(NonEmptyLists{ix->cand_off.as<uint32_t>()}, Count{n_lists, nullptr},
-                                          ws.as<uint64_t>());
-    k_scan_blocks<<<1, kBlockThreads, 0, s>>>(ws.as<uint64_t>(), Count{n_lists, nullptr}, ws.as<uint64_t>() + nb,
-                                              d_total + 1);
-    BUILD_TRY(hipGetLastError());
-  }
-  uint32_t h_misc[2] = {0, 0};
-  uint64_t h_unique = 0;
-  uint8_t zmask = 0;
-  BUILD_TRY(hipMemcpyAsync(h_misc, misc.p, 8, hipMemcpyDeviceToHost, s));
-  BUILD_TRY(hipMemcpyAsync(&h_unique, d_total + 1, 8, hipMemcpyDeviceToHost, s));
-  BUILD_TRY(hipMemcpyAsync(&zmask, ix->tau_mask.as<uint8_t>() + ix->n_slots, 1, hipMemcpyDeviceToHost, s));
+  struct {
+    uint32_t overflow, failed;
+    uint64_t total;   // masters listed, and in the high half the non-empty lists = distinct signatures
+    uint32_t zero_mask;
+  } h{};
+  BUILD_TRY(hipMemcpyAsync(&h, misc.p, sizeof h, hipMemcpyDeviceToHost, s));
   BUILD_TRY(hipStreamSynchronize(s));
 #undef BUILD_TRY
-  if (h_misc[1]) return bail2(fail(CARVE_EDEVICE, "build_master_index: %u keys could not be placed", h_misc[1]));
-  ix->n_overflow = h_misc[0];
+  if (h.failed) return bail2(fail(CARVE_EDEVICE, "build_master_index: %u keys could not be placed", h.failed));
+  const uint64_t h_unique = h.total >> 32;
+  const uint32_t zmask = h.zero_mask;
+  ix->n_overflow = h.overflow;
   ix->zero_sig_mask = zmask;
   ix->n_unique = h_unique;
   {   // prefilter: words of 64 bits, a power of two of them
@@ -1913,13 +1937,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     }
     if (unit == kFragBytes && lw > 29) lw = 29;   // fragment filters: at most 2^30 words of 32 bits
     if (lw > 0 && lw <= 32) {
-      if ((rc = ix->bloom.reserve(8ull << lw))) return bail2(rc);
       ix->log2_bloom_words = lw;
-      if (hipMemsetAsync(ix->bloom.p, 0, 8ull << lw, s) != hipSuccess)
-        return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom memset failed"));
-      if (unit == kFragBytes)   // the same bytes as 2^(lw+1) words of 32 bits, 3 bits per signature
-        k_frag_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->n_slots, lw + 1,
-                                                                   zmask ? 1u : 0u, ix->bloom.as<uint32_t>());
       // The filter split by position (sector indexes): slice t holds the keys
       // with a master at position t, about an eighth of them, and each XCD of a
       // position-split scan keeps only its slice in L2, so the slices are sized
@@ -1929,22 +1947,28 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
       // false positives send 16% of the sectors to the table); else the
       // requested bits per key. At least 2 words per slice (bloom_place needs
       // log2_words >= 1: its shift by 64 - log2_words).
+      constexpr uint64_t kSliceAutoBytes = 4ull << 20;
+      uint32_t ls = 1;
+      const uint64_t bits = p.bloom_bits_per_key ? p.bloom_bits_per_key : 16;
+      while (ls < 32 && (64ull << ls) < bits * cdiv(keys_n, kPositions) &&
+             (p.bloom_bits_per_key || (8ull << (ls + 1)) <= kSliceAutoBytes))
+        ++ls;
       if (unit == kSectorBytes) {
-        constexpr uint64_t kSliceAutoBytes = 4ull << 20;
-        const uint64_t per_slice = cdiv(keys_n, kPositions);
-        const uint64_t bits = p.bloom_bits_per_key ? p.bloom_bits_per_key : 16;
-        uint32_t ls = 1;
-        while (ls < 32 && (64ull << ls) < bits * per_slice &&
-               (p.bloom_bits_per_key || (8ull << (ls + 1)) <= kSliceAutoBytes))
-          ++ls;
-        if ((rc = ix->bloom_tau.reserve((8ull * kPositions) << ls))) return bail2(rc);
+        rc = carve_up(ix->filters, {{&ix->bloom, 8ull << lw}, {&ix->bloom_tau, (8ull * kPositions) << ls}});
         ix->log2_bloom_tau = ls;
-        if (hipMemsetAsync(ix->bloom_tau.p, 0, (8ull * kPositions) << ls, s) != hipSuccess)
-          return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom memset failed"));
+      } else {
+        rc = carve_up(ix->filters, {{&ix->bloom, 8ull << lw}});
+      }
+      if (rc) return bail2(rc);
+      if (hipMemsetAsync(ix->filters.p, 0, ix->filters.bytes, s) != hipSuccess)
+        return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom memset failed"));
+      if (unit == kFragBytes)   // the same bytes as 2^(lw+1) words of 32 bits, 3 bits per signature
+        k_frag_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->n_slots, lw + 1,
+                                                                   zmask ? 1u : 0u, ix->bloom.as<uint32_t>());
+      else
         k_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->tau_mask.as<uint8_t>(),
                                                             ix->n_slots, lw, ix->bloom.as<uint64_t>(), ls,
                                                             ix->bloom_tau.as<uint64_t>());
-      }
       if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom build failed"));
     }
@@ -1965,7 +1989,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
       return bail2(fail(CARVE_EDEVICE, "build_fragment_index: filter build failed"));
   }
-  cleanup();
+  work.release();
   *out = ix;
   return CARVE_OK;
 }

@@ -108,8 +108,8 @@ typedef struct {
 
 typedef struct {
   uint32_t blocks_per_cu;   /* work-groups of the persistent scan grid per compute unit; 0 = no cap: as many as
-                               serve the scan (a djb2 scan that does not ask for runs of tiles either is then
-                               launched with a wave per 16 sectors, which the hardware hands out) */
+                               serve the scan (one that does not ask for runs of tiles either is then launched
+                               with waves for all of its sectors, which the hardware hands out) */
   uint32_t tiles_per_chunk; /* consecutive 64-sector tiles a wave takes before striding (the split walk also
                                hands out the last eighth of each position's tiles in runs of this length); 0 = 1 */
   uint32_t split;           /* carve_split_mode: how scans of one image under the per-cluster rule walk it */

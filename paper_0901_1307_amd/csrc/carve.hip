@@ -1118,27 +1118,23 @@ int scan_counts(const Items& items, uint32_t* out, uint64_t n, uint64_t* d_total
   return CARVE_OK;
 }
 
-// A djb2 scan takes the kernels with a wave per 16 sectors unless its launch
-// shape asks for something else (a cap on the grid, runs of tiles), or its grid
-// would be too large.
-template <int kSig>
-bool scan_by_parts(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
-  return kSig == kSigDjb2 && !per_cu_cap && chunk <= 1 && n_tiles * kTileParts <= kMaxPartBlocks;
+// A scan takes the kernels without a loop (a wave per 16 sectors, or for the CRC
+// per tile) unless its launch shape asks for something else (a cap on the grid,
+// runs of tiles), or its grid would be too large.
+bool scan_without_loop(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
+  return !per_cu_cap && chunk <= 1 && n_tiles * kTileParts <= kMaxPartBlocks;
 }
-// The CRC's persistent grid when the launch shape leaves it open: 2 blocks per
-// CU, half of what fits (2 GiB: 324 against 339 us, 64 MiB the same).
-constexpr uint32_t kCrcBlocksPerCu = 2;
 
 template <int kMode, int kSig, int kLayout, class Src>
 void launch_k_scan_as(const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap, const IndexView& ix,
                       uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
-  if constexpr (kSig == kSigDjb2) {
-    if (scan_by_parts<kSig>(per_cu_cap, chunk, n_tiles)) {
+  if (scan_without_loop(per_cu_cap, chunk, n_tiles)) {
+    if constexpr (kSig == kSigDjb2)
       k_scan_parts<kMode, Src, kLayout><<<(unsigned)(n_tiles * kTileParts), kWave, 0, s>>>(src, ix, out, hit_slot);
-      return;
-    }
-  } else if (!per_cu_cap) {
-    per_cu_cap = kCrcBlocksPerCu;
+    else
+      k_scan_tiles<kMode, Src, kLayout><<<(unsigned)cdiv(n_tiles, kScanWaves), kScanThreads, 0, s>>>(src, n_tiles, ix,
+                                                                                                    out, hit_slot);
+    return;
   }
   const uint64_t want = cdiv(cdiv(n_tiles, chunk), kScanWaves);
   const int grid = resident_grid(k_scan<kMode, kSig, Src, kLayout>, kScanThreads, want, per_cu_cap);
@@ -1175,14 +1171,14 @@ template <int kSig, int kLayout, bool kSlots>
 void launch_k_scan_tau_as(const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk, uint32_t per_cu_cap,
                           const IndexView& ix, uint64_t* tau_words, uint32_t* hit_slot, uint64_t* ctr,
                           hipStream_t s) {
-  if constexpr (kSig == kSigDjb2) {
-    if (scan_by_parts<kSig>(per_cu_cap, chunk, kPositions * words_per_pos)) {
+  if (scan_without_loop(per_cu_cap, chunk, kPositions * words_per_pos)) {
+    if constexpr (kSig == kSigDjb2)
       k_scan_tau_parts<kLayout, kSlots><<<(unsigned)(kPositions * words_per_pos * kTileParts), kWave, 0, s>>>(
           d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
-      return;
-    }
-  } else if (!per_cu_cap) {
-    per_cu_cap = kCrcBlocksPerCu;
+    else
+      k_scan_tau_tiles<kLayout, kSlots><<<(unsigned)(kPositions * cdiv(words_per_pos, kScanWaves)), kScanThreads, 0, s>>>(
+          d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
+    return;
   }
   const uint64_t want = kPositions * cdiv(cdiv(words_per_pos, chunk), kScanWaves);
   int grid = resident_grid(k_scan_tau<kSig, kLayout, kSlots>, kScanThreads, want, per_cu_cap);

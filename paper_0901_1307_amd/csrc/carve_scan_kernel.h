@@ -141,8 +141,8 @@ struct TileHash<kSigCrc64> {
 };
 
 // ------------------------------------------------------------------ scan
-// Persistent grid over the tile space (the CRC, and djb2 with a launch shape
-// that caps the grid or asks for runs of tiles): wave q takes chunks q, q + W, ... of
+// Persistent grid over the tile space (for launch shapes that cap the grid or
+// ask for runs of tiles): wave q takes chunks q, q + W, ... of
 // `chunk` consecutive tiles (W = waves in the grid). 4 waves per SIMD (at
 // most 128 VGPRs): the more waves, the more sector loads in flight per CU.
 // kLayout: the index's probe layout (kFlags only).
@@ -234,6 +234,35 @@ __device__ __forceinline__ void scan_part(const Rows& rows, uint32_t part, uint3
 // Sectors of a part that starts `first` sectors into a tile of n.
 __device__ __forceinline__ uint32_t part_valid(uint64_t n, uint64_t first) {
   return n <= first ? 0u : (n - first < kPart ? (uint32_t)(n - first) : kPart);
+}
+
+// The CRC's counterpart: a wave per tile of 64 sectors, since the CRC is a chain
+// over a sector's bytes that one lane runs; four waves to a block (their staging
+// areas are what bounds the waves of a CU, at 16). Against the persistent grid at
+// its best shape (2 blocks per CU): 1 MiB 7.9 -> 7.1 us, 700 MiB 120 -> 115, 2 GB
+// 330 -> 313, 8 GiB 1307 -> 1249; one wave to a block: 7.0, 117, 318, 1268.
+template <int kMode, class Src, int kLayout>
+__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan_tiles(
+    Src src, uint64_t n_tiles, IndexView ix, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const uint32_t l = lane_id();
+  TileHash<kSigCrc64> hash(w);
+  const uint64_t g = (uint64_t)blockIdx.x * kScanWaves + w;
+  if (g >= n_tiles) return;
+  const TileRef tr = src.tile_at(g);
+  const ContiguousRows rows{tr.base, tr.n_valid};
+  PhaseRegs A, B;
+  hash.load(rows, A);
+  const uint64_t h = hash.tile(rows, A, B, [](PhaseRegs&) {});
+  if constexpr (kMode == kSigs) {
+    if (l < tr.n_valid) out[g * kTileSectors + l] = h;
+  } else {
+    uint64_t hits = tile_probe<kLayout, 1, kMode == kFlags>(
+        ix, h, (tr.tau_first + l) & (kClusterSectors - 1), tr.any_tau != 0,
+        kMode == kFlags ? hit_slot + g * kTileSectors : nullptr, ix.bloom, ix.log2_bloom_words);
+    if (tr.n_valid < kTileSectors) hits &= (1ull << tr.n_valid) - 1ull;
+    if (l == 0) out[g] = hits;
+  }
 }
 
 // Block b takes part b mod 4 of tile b / 4.
@@ -431,6 +460,33 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void
                                                ix.bloom_tau + ((uint64_t)p << ix.log2_bloom_tau), ix.log2_bloom_tau,
                                                tau_words + p * words_per_pos + g,
                                                kSlots ? hit_slot + (k0 * kPositions + r) : nullptr);
+}
+
+// And for k_scan_tiles': block b takes tiles 4(b / 8).. of position b mod 8.
+template <int kLayout, bool kSlots>
+__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan_tau_tiles(
+    const uint8_t* __restrict__ image, uint64_t n_sectors, uint32_t tau0, uint64_t words_per_pos, IndexView ix,
+    uint64_t* __restrict__ tau_words, uint32_t* __restrict__ hit_slot) {
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const uint32_t p = blockIdx.x % kPositions, r = (p - tau0) & (kPositions - 1);
+  TileHash<kSigCrc64> hash(w);
+  const uint64_t g = (uint64_t)(blockIdx.x / kPositions) * kScanWaves + w;
+  if (g >= words_per_pos) return;
+  const uint64_t k0 = g * kTileSectors;   // its first cluster
+  const uint64_t count = position_count(n_sectors, r);
+  uint64_t hits = 0;
+  if (count > k0) {
+    const uint32_t n = count - k0 < kTileSectors ? (uint32_t)(count - k0) : kTileSectors;
+    const ClusterStrideRows rows{image + (k0 * kPositions + r) * kSectorBytes, n};
+    PhaseRegs A, B;
+    hash.load(rows, A);
+    const uint64_t h = hash.tile(rows, A, B, [](PhaseRegs&) {});
+    hits = tile_probe<kLayout, kPositions, kSlots, true>(
+        ix, h, p, false, kSlots ? hit_slot + (k0 * kPositions + r) : nullptr,
+        ix.bloom_tau + ((uint64_t)p << ix.log2_bloom_tau), ix.log2_bloom_tau);
+    if (n < kTileSectors) hits &= (1ull << n) - 1ull;
+  }
+  if (lane_id() == 0) tau_words[p * words_per_pos + g] = hits;
 }
 
 }  // namespace carve

@@ -182,13 +182,16 @@ def read_ceiling(image, split: bool, reps: int = 3) -> dict:
             "sweep_GBps": {str(b): round(r, 1) for r, b, _ in rows}}
 
 
-def scan_kernel_name(idx) -> str:
-    """The kernel a per-cluster scan of one image runs with this index."""
+def scan_kernel_name(idx, sig_kind) -> str:
+    """The kernel a per-cluster scan of one large image runs with this index."""
     from paper_0901_1307_amd import carve
-    split = idx.scan_config()["split"]
-    big = idx.stats()["bloom_bytes"] >= (4 << 20)
-    on = split == carve.CARVE_SPLIT_ON or (split == carve.CARVE_SPLIT_AUTO and big)
-    return "k_scan_tau" if on and idx.stats()["bloom_bytes"] else "k_scan"
+    shape = idx.scan_config()
+    big = idx.stats()["bloom_bytes"] >= (8 << 20)
+    on = shape["split"] == carve.CARVE_SPLIT_ON or (shape["split"] == carve.CARVE_SPLIT_AUTO and big)
+    name = "k_scan_tau" if on and idx.stats()["bloom_bytes"] else "k_scan"
+    if shape["blocks_per_cu"] or shape["tiles_per_chunk"] > 1:
+        return name   # a launch shape that asks for a persistent grid
+    return name + ("_tiles" if sig_kind == carve.CARVE_SIG_CRC64_ISO else "_parts")
 
 
 class StepLanes:
@@ -323,7 +326,7 @@ def run_plain(args, config: str, with_cpu: bool, with_ceiling: bool, also_in_fli
         del sample
         log(f"[bench] autotuned in {time.perf_counter() - t0:.2f} s: {pick}; index {idx.stats()}")
     shape = idx.scan_config()
-    kernel = scan_kernel_name(idx)
+    kernel = scan_kernel_name(idx, sig_kind)
 
     n_sectors = cfg.n_disk_sectors
     image_bytes = img.data.numel()
@@ -427,7 +430,7 @@ def run_plain(args, config: str, with_cpu: bool, with_ceiling: bool, also_in_fli
         "roofline": {
             "bound": "hbm",
             "kernel": (f"{kernel} (signature + probe"
-                       + (", split by cluster position over the 8 XCDs)" if kernel == "k_scan_tau" else ")")),
+                       + (", split by cluster position over the 8 XCDs)" if kernel.startswith("k_scan_tau") else ")")),
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -873,7 +876,7 @@ def run_fragments(args):
         "windows_per_s": round(n_windows / (ms_per_step * 1e-3)),
         "steps_in_flight": inflight, "ms_per_step_one_in_flight": serial,
         "flagged": n_flag, "confirmed": n_match,
-        "roofline": {"bound": "hbm", "kernel": "k_frag_scan (rolling signatures + filter/table probe)",
+        "roofline": {"bound": "hbm", "kernel": "k_frag_scan (signatures on the matrix units + filter/table probe)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel_ms": round(k_avg, 4),
                      # the kernel alone: the same kernel in the steps run one at a time

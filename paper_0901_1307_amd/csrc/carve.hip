@@ -1544,9 +1544,10 @@ void launch_confirm_emit(carve_scan* sc, const Src& src, const ConfirmView& cv, 
 }
 
 // Enqueue the confirmation of every flagged unit of the scan: the equal
-// counts and masks (k_confirm_count), then the records (k_confirm_emit). The number of flagged units is not read back: the kernels
-// take it from the device, and buffers are sized for the most there can be,
-// so nothing here waits. Records go to the scan's own buffer, or (dest !=
+// counts and masks (k_confirm_count), then the records (k_confirm_emit). The
+// number of flagged units is not read back: the kernels take it from the
+// device, and buffers are sized for the most there can be, so nothing here
+// waits. Records go to the scan's own buffer, or (dest !=
 // null: device memory of the caller, dest_cap records) straight to their
 // destination.
 template <class Src, class Rec>

@@ -290,8 +290,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void
 }
 
 // ------------------------------------------------- position-split scan
-// ------------------------------------------------- position-split scan
-// ------------------------------------------------- position-split scan
 // One image, per-cluster rule, split by cluster position. Workgroups are
 // dispatched to the chip's 8 XCDs in turn (block b runs on XCD b mod 8), so
 // block b scans the sectors at position p = b mod 8 and probes position p's

@@ -189,9 +189,16 @@ def scan_kernel_name(idx, sig_kind) -> str:
     big = idx.stats()["bloom_bytes"] >= (8 << 20)
     on = shape["split"] == carve.CARVE_SPLIT_ON or (shape["split"] == carve.CARVE_SPLIT_AUTO and big)
     name = "k_scan_tau" if on and idx.stats()["bloom_bytes"] else "k_scan"
+    return name + scan_kernel_form(shape, sig_kind)
+
+
+def scan_kernel_form(shape, sig_kind) -> str:
+    """What a launch shape adds to the kernel's name: nothing for a persistent
+    grid (a cap on it, or runs of tiles), else the waves' share."""
+    from paper_0901_1307_amd import carve
     if shape["blocks_per_cu"] or shape["tiles_per_chunk"] > 1:
-        return name   # a launch shape that asks for a persistent grid
-    return name + ("_tiles" if sig_kind == carve.CARVE_SIG_CRC64_ISO else "_parts")
+        return ""
+    return "_tiles" if sig_kind == carve.CARVE_SIG_CRC64_ISO else "_parts"
 
 
 class StepLanes:
@@ -446,8 +453,8 @@ def run_plain(args, config: str, with_cpu: bool, with_ceiling: bool, also_in_fli
         },
     }
     if with_ceiling:
-        ceil = read_ceiling(img.data, split=kernel == "k_scan_tau")
-        other = read_ceiling(img.data, split=kernel != "k_scan_tau")
+        ceil = read_ceiling(img.data, split=kernel.startswith("k_scan_tau"))
+        other = read_ceiling(img.data, split=not kernel.startswith("k_scan_tau"))
         log(f"[bench] streaming-read ceiling ({ceil['pattern']}): {ceil['GBps']:.0f} GB/s; "
             f"{other['pattern']}: {other['GBps']:.0f} GB/s")
         out["roofline"]["read_ceiling"] = ceil
@@ -533,10 +540,11 @@ def run_batched(args) -> dict:
         "vs_baseline": None, "dtype": DTYPE, "data": "synthetic",
         "config": {"workload": (f"batched: {len(images)} device-resident images, sizes log-uniform 1 MiB-1 GiB "
                                 f"({total / 2**30:.1f} GiB), hit rate 0-5% each, against the mid master set "
-                                f"({cfg.n_master_sectors} sectors); one persistent launch replayed from a HIP graph"),
+                                f"({cfg.n_master_sectors} sectors); one launch replayed from a HIP graph"),
                    "image_bytes": total, "n_images": len(images), "launch_shape": tuned, "index_pick": pick},
         "flagged": n_flag, "confirmed": n_match,
-        "roofline": {"bound": "hbm", "kernel": "k_scan<kFlags, ManyImages>", "achieved": round(achieved, 1),
+        "roofline": {"bound": "hbm", "kernel": f"k_scan{scan_kernel_form(idx.scan_config(), carve.CARVE_SIG_DJB2_64)}<kFlags, ManyImages>",
+                     "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None, "kernel_ms": round(k_avg, 4)},
     }

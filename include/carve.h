@@ -204,11 +204,13 @@ int confirm_matches(const carve_index* idx, carve_scan* sc, carve_match* out, ui
  * enqueued, or captured in a HIP graph, ahead of any readback. Calling
  * confirm_matches without it enqueues the work itself.
  * Graphs: a scan replayed from a captured graph runs no host code, so the
- * scan marks on the device that its confirmation is still to be done, and
- * confirm_matches checks that mark (one 8-byte readback) before reusing a
- * confirmation enqueued earlier: after replaying a graph that holds only the
- * scan, confirm_matches confirms the replayed scan; a graph that holds scan
- * and confirm_enqueue leaves only the copy to it.
+ * scan marks that its confirmation is still to be done, a confirmation leaves
+ * its own mark, and confirm_matches goes by that mark: after replaying a graph
+ * that holds only the scan, it confirms the replayed scan; a graph that holds
+ * scan and confirm_enqueue leaves only the copy to it. Where a replay has more
+ * records (or flagged windows) than the captured confirmation has room for,
+ * confirm_matches produces them in other buffers: what the graph writes to
+ * stays where it is.
  */
 int confirm_enqueue(const carve_index* idx, carve_scan* sc);
 

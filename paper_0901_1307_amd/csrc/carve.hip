@@ -32,6 +32,7 @@
 
 #include <algorithm>
 #include <initializer_list>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -73,14 +74,15 @@ constexpr uint64_t kDirectWords = 16384;   // hit words compacted by one launch 
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;   // master whose key could not be placed
 
 // A scan object's counters: [0] flagged units, [1] confirmed records,
-// [kConfirmedWord] 1 once a confirmation ran after the latest scan. The first
-// two are kept on the device, where later kernels read them, and all three in
-// pinned host memory, written there by the kernels that finish them: the host
-// reads them after a synchronization with no copy enqueued for it (a 64 MiB
-// disk's step 51 -> 48 us together with the scan's ordering event, below). Every
-// scan's compaction clears the marker, so a scan replayed from a captured graph
-// (which runs no host code) still invalidates an earlier confirmation; the
-// host checks it before reusing one.
+// [kConfirmedWord] the tag of the confirmation that ran after the latest scan,
+// or 0 when none did. The first two are kept on the device, where later kernels
+// read them, and all three in pinned host memory, written there by the kernels
+// that finish them: the host reads them after a synchronization with no copy
+// enqueued for it (a 64 MiB disk's step 51 -> 48 us together with the scan's
+// ordering event, below). Every scan's compaction clears the tag, so a scan
+// replayed from a captured graph (which runs no host code) still invalidates an
+// earlier confirmation; and a confirmation replayed from one leaves its own tag,
+// by which the host knows where that one wrote its records.
 constexpr uint32_t kConfirmedWord = 2;
 
 // Timed launches whose kernel durations a scan object keeps (the most recent).
@@ -874,7 +876,7 @@ __device__ __forceinline__ void put_record(carve_batch_match* out, uint64_t pos,
 // k_confirm_count, so the same grid): its confirmed matches, in candidate (=
 // file, sector-in-file) order, behind those of the units before it; records
 // past `cap` are counted but not written. *total and host[1] receive the number
-// of records, host[kConfirmedWord] the mark (see kConfirmedWord).
+// of records, host[kConfirmedWord] the confirmation's tag.
 template <class Src, class Rec>
 __global__ __launch_bounds__(kBlockThreads) void k_confirm_emit(Src src, const uint64_t* __restrict__ ids,
                                                                const uint32_t* __restrict__ img_of, Count count,
@@ -884,14 +886,14 @@ __global__ __launch_bounds__(kBlockThreads) void k_confirm_emit(Src src, const u
                                                                const uint64_t* __restrict__ range_sums,
                                                                Rec* __restrict__ out, uint64_t cap,
                                                                uint64_t* __restrict__ total,
-                                                               uint64_t* __restrict__ host) {
+                                                               uint64_t* __restrict__ host, uint64_t tag) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
   const uint64_t n_flagged = count.get();
   const UnitRange range = confirm_range<Src>(n_flagged);
   auto finish = [&](uint64_t records) {
     *total = records;
     host[1] = records;
-    host[kConfirmedWord] = 1;
+    host[kConfirmedWord] = tag;
   };
   if (range.begin >= range.end) {
     if (n_flagged == 0 && blockIdx.x == 0 && threadIdx.x == 0) finish(0);
@@ -1289,6 +1291,25 @@ struct carve_index {
   }
 };
 
+// What a confirmation keeps per flagged unit and its records.
+struct ConfirmBufs {
+  DevBuf mem, n_match, match_mask, range_sums, matches;   // the others are parts of mem
+  void release() {
+    for (DevBuf* b : {&n_match, &match_mask, &range_sums, &matches, &mem}) b->release();
+  }
+};
+// An enqueued confirmation, and where its records go: bufs->matches (rec_cap of
+// them), or a caller's device buffer (dest, dest_cap records).
+struct ConfirmRun {
+  uint64_t tag = 0;
+  ConfirmBufs* bufs = nullptr;
+  uint32_t grid = 0;    // its blocks (= ranges)
+  uint64_t room = 0;    // flagged units it has room for
+  uint64_t rec_cap = 0;
+  void* dest = nullptr;
+  uint64_t dest_cap = 0;
+};
+
 // Results of one scan (one image, or a batch of them).
 struct carve_scan {
   int device = 0;
@@ -1308,17 +1329,18 @@ struct carve_scan {
   DevBuf bitmap, ws, ids, img_of, count, hit_slot, img_off;   // hit_slot: matched slot of each flagged sector
   DevBuf tau_words;   // one image, per-cluster rule: the hit words of the position-split scan
   HostBuf h_count, h_img_off;                                 // pinned: the counters, a readback
-  // confirmation: records go to `matches` (rec_cap of them) or to a caller's
-  // device buffer (conf_dest, conf_dest_cap records)
-  DevBuf n_match, match_mask, matches, range_sums;
-  DevBuf scan_mem, conf_mem;   // what the buffers above are parts of (but a regrown `matches`)
-  uint32_t conf_grid = 0;        // blocks (= ranges) of the last enqueued confirmation
-  uint64_t conf_room = 0;        // flagged units the last enqueued confirmation had room for
+  DevBuf scan_mem;   // what the scan's buffers above are parts of
+  // confirmation: the last buffers are the ones in use, earlier ones belong to captured confirmations
+  std::vector<std::unique_ptr<ConfirmBufs>> conf;
+  ConfirmRun run;                    // the latest enqueued confirmation
+  std::vector<ConfirmRun> captured;  // those captured into graphs (equal ones share a tag)
+  uint64_t last_tag = 0;
   uint64_t conf_need = 0;        // the most flagged units a confirmation of this object has met
+  uint64_t rec_need = 0;         // and the most records asked for
   bool confirm_enqueued = false;
-  uint64_t rec_cap = 0;
-  void* conf_dest = nullptr;
-  uint64_t conf_dest_cap = 0;
+  // records that had to be produced again for one copy (past their room, or written elsewhere)
+  DevBuf again;
+  uint64_t again_tag = 0, again_n = 0;
   // timing: launch k brackets its scan kernel with ev[2 (k mod kTimedRing)]
   // and ev[2 (k mod kTimedRing) + 1]; n_timed launches so far
   std::vector<hipEvent_t> ev;
@@ -1536,30 +1558,49 @@ int read_flagged(carve_scan* sc, uint64_t* n) {
   return CARVE_OK;
 }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // (the null stream cannot be captured)
+  return false;
+}
+
 // Confirmation buffers for up to cap_f flagged units. Records: room for
-// about one per eighth of the units (more are counted, and produced again
-// with their exact count when they are copied out). Returns the record room.
+// about one per eighth of the units, or what was asked for before (more are
+// counted, and produced again with their exact count when they are copied out).
+// A captured confirmation's buffers stay as they are: where they are too small,
+// later confirmations get others.
 template <class Rec>
-int reserve_confirm(carve_scan* sc, uint64_t cap_f, uint64_t* rec_room) {
-  uint64_t rec_cap = sc->matches.bytes / sizeof(Rec);
-  if (rec_cap < cap_f / 8 + 4096) rec_cap = cap_f / 8 + 4096;
-  CARVE_TRY(reserve_parts(sc->conf_mem, {{&sc->n_match, cap_f * 4},
-                                         {&sc->match_mask, cap_f * 8},
-                                         {&sc->range_sums, kConfirmRanges * sizeof(uint64_t)},
-                                         {&sc->matches, rec_cap * sizeof(Rec)}}));
+int reserve_confirm(carve_scan* sc, uint64_t cap_f, ConfirmBufs** bufs, uint64_t* rec_room) {
+  if (sc->conf.empty()) sc->conf.emplace_back(new ConfirmBufs());
+  ConfirmBufs* b = sc->conf.back().get();
+  const uint64_t rec_cap = std::max<uint64_t>({b->matches.bytes / sizeof(Rec), cap_f / 8 + 4096, sc->rec_need});
+  const uint64_t sums = kConfirmRanges * sizeof(uint64_t);
+  const bool fits = cap_f * 4 <= b->n_match.bytes && cap_f * 8 <= b->match_mask.bytes &&
+                    sums <= b->range_sums.bytes && rec_cap * sizeof(Rec) <= b->matches.bytes;
+  bool in_graph = false;
+  for (const ConfirmRun& r : sc->captured) in_graph = in_graph || r.bufs == b;
+  if (!fits && in_graph) {
+    sc->conf.emplace_back(new ConfirmBufs());
+    b = sc->conf.back().get();
+  }
+  CARVE_TRY(reserve_parts(b->mem, {{&b->n_match, cap_f * 4},
+                                   {&b->match_mask, cap_f * 8},
+                                   {&b->range_sums, sums},
+                                   {&b->matches, rec_cap * sizeof(Rec)}}));
+  *bufs = b;
   *rec_room = rec_cap;
   return CARVE_OK;
 }
 
-// The records of the scan's latest k_confirm_count (nf: its flagged units),
-// with its grid.
+// The records of confirmation r's k_confirm_count (nf: its flagged units).
 template <class Src, class Rec>
-void launch_confirm_emit(carve_scan* sc, const Src& src, const ConfirmView& cv, const Count& nf, Rec* out,
-                         uint64_t cap) {
-  k_confirm_emit<Src, Rec><<<sc->conf_grid, kBlockThreads, 0, sc->stream>>>(
+void launch_confirm_emit(carve_scan* sc, const Src& src, const ConfirmView& cv, const Count& nf, const ConfirmRun& r,
+                         Rec* out, uint64_t cap) {
+  k_confirm_emit<Src, Rec><<<r.grid, kBlockThreads, 0, sc->stream>>>(
       src, sc->ids.as<uint64_t>(), sc->batch ? sc->img_of.as<uint32_t>() : nullptr, nf, sc->hit_slot.as<uint32_t>(),
-      cv, sc->n_match.as<uint32_t>(), sc->match_mask.as<uint64_t>(), sc->range_sums.as<uint64_t>(), out, cap,
-      sc->count.as<uint64_t>() + 1, sc->h_count.as<uint64_t>());
+      cv, r.bufs->n_match.as<uint32_t>(), r.bufs->match_mask.as<uint64_t>(), r.bufs->range_sums.as<uint64_t>(), out,
+      cap, sc->count.as<uint64_t>() + 1, sc->h_count.as<uint64_t>(), r.tag);
 }
 
 // Enqueue the confirmation of every flagged unit of the scan: the equal
@@ -1574,9 +1615,7 @@ int confirm_enqueue_impl(const carve_index* idx, carve_scan* sc, const Src& src,
                          uint64_t dest_cap = 0) {
   hipStream_t s = sc->stream;
   sc->confirm_enqueued = true;
-  sc->rec_cap = 0;
-  sc->conf_dest = dest;
-  sc->conf_dest_cap = dest ? dest_cap : 0;
+  sc->run = ConfirmRun{};
   if (sc->n_tiles == 0) return CARVE_OK;
   // Flagged units are at most `most`. A sector scan's per-flagged arrays have
   // room for all of them; a fragment scan's for an eighth of its windows (at
@@ -1590,22 +1629,49 @@ int confirm_enqueue_impl(const carve_index* idx, carve_scan* sc, const Src& src,
     if (room < sc->conf_need) room = sc->conf_need;
     if (room < cap_f) cap_f = room;
   }
-  sc->conf_room = cap_f;
-  const uint64_t* d_count = sc->count.as<uint64_t>();
-  uint64_t rec_cap = 0;
-  CARVE_TRY(reserve_confirm<Rec>(sc, cap_f, &rec_cap));
-  sc->rec_cap = dest ? 0 : rec_cap;
-  const ConfirmView cv = idx->cview();
-  const uint32_t* img_of = sc->batch ? sc->img_of.as<uint32_t>() : nullptr;
-  const Count nf{cap_f, d_count};
+  ConfirmRun r;
+  r.room = cap_f;
+  CARVE_TRY(reserve_confirm<Rec>(sc, cap_f, &r.bufs, &r.rec_cap));
+  if (dest) {
+    r.rec_cap = 0;
+    r.dest = dest;
+    r.dest_cap = dest_cap;
+  }
   const uint64_t most_ranges = cdiv(cap_f, confirm_pass<Src>());
-  sc->conf_grid = most_ranges < kConfirmRanges ? (uint32_t)most_ranges : kConfirmRanges;
-  k_confirm_count<Src><<<sc->conf_grid, kBlockThreads, 0, s>>>(
-      src, sc->ids.as<uint64_t>(), img_of, nf, sc->hit_slot.as<uint32_t>(), cv, sc->n_match.as<uint32_t>(),
-      sc->match_mask.as<uint64_t>(), sc->range_sums.as<uint64_t>());
-  launch_confirm_emit(sc, src, cv, nf, dest ? dest : sc->matches.as<Rec>(), dest ? dest_cap : rec_cap);
+  r.grid = most_ranges < kConfirmRanges ? (uint32_t)most_ranges : kConfirmRanges;
+  if (capturing(s)) {   // the tag of an equal one, so that capturing again and again keeps one entry
+    for (const ConfirmRun& c : sc->captured)
+      if (c.bufs == r.bufs && c.grid == r.grid && c.room == r.room && c.rec_cap == r.rec_cap && c.dest == r.dest &&
+          c.dest_cap == r.dest_cap)
+        r.tag = c.tag;
+    if (!r.tag) {
+      r.tag = ++sc->last_tag;
+      sc->captured.push_back(r);
+    }
+  } else {
+    r.tag = ++sc->last_tag;
+  }
+  const ConfirmView cv = idx->cview();
+  const Count nf{cap_f, sc->count.as<uint64_t>()};
+  k_confirm_count<Src><<<r.grid, kBlockThreads, 0, s>>>(
+      src, sc->ids.as<uint64_t>(), sc->batch ? sc->img_of.as<uint32_t>() : nullptr, nf, sc->hit_slot.as<uint32_t>(),
+      cv, r.bufs->n_match.as<uint32_t>(), r.bufs->match_mask.as<uint64_t>(), r.bufs->range_sums.as<uint64_t>());
+  launch_confirm_emit(sc, src, cv, nf, r, dest ? dest : r.bufs->matches.as<Rec>(), dest ? dest_cap : r.rec_cap);
   HIP_TRY(hipGetLastError());
+  sc->run = r;
   return CARVE_OK;
+}
+
+// The confirmation with this tag: the latest one, or one replayed from a graph.
+const ConfirmRun* confirmed_by(const carve_scan* sc, uint64_t tag, bool* replayed) {
+  *replayed = false;
+  if (!tag) return nullptr;
+  for (const ConfirmRun& r : sc->captured)
+    if (r.tag == tag) {
+      *replayed = true;
+      return &r;
+    }
+  return sc->run.tag == tag ? &sc->run : nullptr;
 }
 
 // Confirmed records of the scan into `out` (host or device): one readback of
@@ -1621,28 +1687,40 @@ int confirm_all(const carve_index* idx, carve_scan* sc, const Src& src, Rec* out
     CARVE_TRY((confirm_enqueue_impl<Src, Rec>(idx, sc, src, to_device ? out : nullptr, cap)));
   if (sc->n_tiles == 0) return CARVE_OK;
   uint64_t c[3];
+  bool replayed = false;
   CARVE_TRY(read_counts(sc, c));
+  const ConfirmRun* run = confirmed_by(sc, c[kConfirmedWord], &replayed);
   // not confirmed since the scan (a scan replayed from a graph after the
   // enqueue), or room for fewer flagged units than there are: again
-  if (!c[kConfirmedWord] || c[0] > sc->conf_room) {
-    if (c[0] > sc->conf_room) sc->conf_need = c[0];
+  if (!run || c[0] > run->room) {
+    if (c[0] > sc->conf_need) sc->conf_need = c[0];
     CARVE_TRY((confirm_enqueue_impl<Src, Rec>(idx, sc, src, to_device ? out : nullptr, cap)));
     CARVE_TRY(read_counts(sc, c));
+    run = confirmed_by(sc, c[kConfirmedWord], &replayed);
+    if (!run) return fail(CARVE_EDEVICE, "confirm: the confirmation did not run");
   }
   const uint64_t nf = c[0], nm = c[1];
   *n_out = nm;
   const uint64_t k = nm < cap ? nm : cap;
-  const bool in_place = sc->conf_dest == (void*)out && k <= sc->conf_dest_cap;
+  const bool in_place = run->dest == (void*)out && k <= run->dest_cap;
   if (k && !in_place) {
-    if (sc->conf_dest || k > sc->rec_cap) {   // records elsewhere, or past the room: produced again, all of them
-      if (k > sc->rec_cap) CARVE_TRY(sc->matches.reserve(k * sizeof(Rec)));
-      sc->rec_cap = sc->matches.bytes / sizeof(Rec);
-      sc->conf_dest = nullptr;
-      sc->conf_dest_cap = 0;
-      launch_confirm_emit(sc, src, idx->cview(), Count{nf, nullptr}, sc->matches.as<Rec>(), sc->rec_cap);
-      HIP_TRY(hipGetLastError());
+    const void* from = run->bufs->matches.p;
+    if (run->dest || k > run->rec_cap) {
+      // Records elsewhere, or past the room: produced again, all of them, in a
+      // buffer of their own. (What a graph writes to stays as it is; the next
+      // confirmation outside of one gets the room.)
+      if (replayed || sc->again_tag != run->tag || sc->again_n < k) {
+        sc->again_tag = 0;
+        CARVE_TRY(sc->again.reserve(k * sizeof(Rec)));
+        launch_confirm_emit(sc, src, idx->cview(), Count{nf, nullptr}, *run, sc->again.as<Rec>(), k);
+        HIP_TRY(hipGetLastError());
+        sc->again_tag = run->tag;
+        sc->again_n = k;
+        if (!run->dest && k > sc->rec_need) sc->rec_need = k;
+      }
+      from = sc->again.p;
     }
-    HIP_TRY(hipMemcpyAsync(out, sc->matches.p, k * sizeof(Rec), hipMemcpyDefault, s));
+    HIP_TRY(hipMemcpyAsync(out, from, k * sizeof(Rec), hipMemcpyDefault, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
   if (nm > cap) return fail(CARVE_ETRUNC, "confirm: %llu matches, capacity %llu", (unsigned long long)nm,
@@ -2041,9 +2119,9 @@ extern "C" void free_scan(carve_scan* sc) {
   if (!sc) return;
   (void)hipStreamSynchronize(sc->stream);
   for (DevBuf* b : {&sc->d_desc, &sc->bitmap, &sc->ids, &sc->img_of, &sc->count, &sc->hit_slot, &sc->img_off,
-                    &sc->tau_words, &sc->ws, &sc->n_match, &sc->match_mask, &sc->range_sums,
-                    &sc->matches, &sc->scan_mem, &sc->conf_mem})
+                    &sc->tau_words, &sc->ws, &sc->scan_mem, &sc->again})
     b->release();
+  for (auto& b : sc->conf) b->release();
   sc->h_desc.release();
   sc->h_count.release();
   sc->h_img_off.release();
@@ -2239,8 +2317,7 @@ extern "C" int scan_batch(const carve_index* idx, const carve_image_desc* images
   int rc;
   if ((rc = reserve_scan(b))) return bail(rc);
   if (!same_desc(desc, b->uploaded)) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(b->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
+    if (capturing(b->stream))
       return bail(fail(CARVE_EINVAL, "scan_batch: new image descriptors while the stream is being captured"));
     const size_t bytes = desc.size() * sizeof(ImageDesc);
     // the staging buffer may still feed the previous upload
@@ -2474,10 +2551,11 @@ CARVE_HIDDEN int carve_batch_reserve(const carve_index* idx, carve_batch** io, u
   const uint32_t keep_images = b->n_images;
   b->n_tiles = tiles;
   b->n_images = n_images;
+  ConfirmBufs* bufs = nullptr;
   uint64_t room = 0;
   const size_t desc_bytes = ((size_t)n_images + 1) * sizeof(ImageDesc);
   int rc = reserve_scan(b);
-  if (rc == CARVE_OK) rc = reserve_confirm<carve_batch_match>(b, tiles * kTileSectors, &room);
+  if (rc == CARVE_OK) rc = reserve_confirm<carve_batch_match>(b, tiles * kTileSectors, &bufs, &room);
   if (rc == CARVE_OK) rc = b->d_desc.reserve(desc_bytes);
   if (rc == CARVE_OK) rc = b->h_desc.reserve(desc_bytes);
   b->n_tiles = keep_tiles;
@@ -2500,13 +2578,13 @@ CARVE_HIDDEN int carve_batch_stage_out(carve_batch* b, int with_matches, const c
   // an empty tile space writes no counts: stage zeros (the offsets are zero-filled)
   const bool counted = b->n_tiles != 0;
   if (!counted) k_fill_u64<<<1, 64, 0, b->stream>>>(b->count.as<uint64_t>(), 2, 0);
-  const uint64_t room = with_matches && counted ? b->rec_cap : 0;
+  const uint64_t room = with_matches && counted ? b->run.rec_cap : 0;
   *match_room = room;
   const uint64_t most = st->ids_cap + 3 * st->match_cap + b->n_images + 1;
   const uint64_t want = cdiv(most, 256);
   k_stage_out<<<(unsigned)(want < 1024 ? (want ? want : 1) : 1024), 256, 0, b->stream>>>(
       b->count.as<uint64_t>(), with_matches, b->n_images, b->img_off.as<uint64_t>(), b->ids.as<uint64_t>(),
-      b->matches.as<uint64_t>(), room, st->totals, st->img_off, st->ids, st->ids_cap, (uint64_t*)st->matches,
+      room ? b->run.bufs->matches.as<uint64_t>() : nullptr, room, st->totals, st->img_off, st->ids, st->ids_cap, (uint64_t*)st->matches,
       st->match_cap);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;

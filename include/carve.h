@@ -170,6 +170,8 @@ int build_master_index(const void* master_sectors, const uint64_t* file_sector_o
  *   io         in: NULL to create a scan object, or a scan object to reuse
  *              (its previous results are discarded; it must not be in use on
  *              another stream). out: the scan object (release with free_scan).
+ *              After a scan that failed while it was being made (ENOMEM, EDEVICE) the object
+ *              holds no results: asking for them is EINVAL until a scan succeeds.
  * Errors: EINVAL (null idx/io, null or misaligned image with n_bytes >= 512,
  * an image in host memory, tau0 > 7, bad tau_mode), ENOMEM, EDEVICE.
  */

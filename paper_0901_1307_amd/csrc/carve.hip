@@ -986,6 +986,7 @@ struct DevBuf {
     size_t sz = need < 256 ? 256 : need;
     if (hipMalloc(&p, sz) != hipSuccess) {
       p = nullptr;
+      (void)hipGetLastError();   // reported here, not by the caller's next launch
       return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
     }
     bytes = sz;
@@ -1052,7 +1053,11 @@ struct HostBuf {
     p = nullptr;
     bytes = 0;
     size_t sz = need < 256 ? 256 : need;
-    if (hipHostMalloc(&p, sz, hipHostMallocDefault) != hipSuccess) return fail(CARVE_ENOMEM, "hipHostMalloc failed");
+    if (hipHostMalloc(&p, sz, hipHostMallocDefault) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+      return fail(CARVE_ENOMEM, "hipHostMalloc failed");
+    }
     bytes = sz;
     return CARVE_OK;
   }
@@ -1348,12 +1353,20 @@ struct carve_scan {
   // record costs the stream about 4 us between the two
   hipEvent_t kernel_done = nullptr;
   bool launched = false;   // a scan kernel was enqueued
+  bool ready = false;      // the latest scan was enqueued whole: false from its start on, and after one that failed
   uint64_t n_timed = 0;
   bool timing = false, timed = false;
 };
 struct carve_batch : carve_scan {};
 
 namespace {
+
+// Whether the object holds (or will hold) a scan's results. A scan that failed,
+// for want of memory say, leaves buffers that were given up to make room, and
+// counts of its own image beside them: nothing may be launched on those.
+int need_results(const carve_scan* sc, const char* who) {
+  return sc->ready ? CARVE_OK : fail(CARVE_EINVAL, "%s: the object's latest scan failed", who);
+}
 
 OneImage one_image(const carve_scan* sc) { return OneImage{sc->desc[0]}; }
 
@@ -2160,12 +2173,14 @@ extern "C" int scan_image(const carve_index* idx, const void* image, uint64_t n_
   sc->fragments = false;
   sc->timed = false;
   sc->confirm_enqueued = false;
+  sc->ready = false;
   int rc = reserve_scan(sc);
   if (rc == CARVE_OK) rc = launch_scan(sc, one_image(sc));
   if (rc != CARVE_OK) {
     if (created) free_scan(sc);
     return rc;
   }
+  sc->ready = true;
   *io = sc;
   return CARVE_OK;
 }
@@ -2270,12 +2285,14 @@ extern "C" int scan_fragments(const carve_index* idx, const void* image, uint64_
   sc->fragments = true;
   sc->timed = false;
   sc->confirm_enqueued = false;
+  sc->ready = false;
   int rc = reserve_scan(sc);
   if (rc == CARVE_OK) rc = launch_scan(sc, fragment_windows(sc));
   if (rc != CARVE_OK) {
     if (created) free_scan(sc);
     return rc;
   }
+  sc->ready = true;
   *io = sc;
   return CARVE_OK;
 }
@@ -2297,6 +2314,9 @@ extern "C" int scan_batch(const carve_index* idx, const carve_image_desc* images
   desc[n_images] = ImageDesc{nullptr, 0, tiles, 0, 0};
   carve_batch* b = *io;
   const bool created = !b;
+  const bool upload = created || !same_desc(desc, b->uploaded);
+  if (upload && capturing((hipStream_t)stream))   // refused before the object changes
+    return fail(CARVE_EINVAL, "scan_batch: new image descriptors while the stream is being captured");
   if (created) {
     b = new carve_batch();
     b->batch = true;
@@ -2314,11 +2334,11 @@ extern "C" int scan_batch(const carve_index* idx, const carve_image_desc* images
   b->desc = desc;
   b->timed = false;
   b->confirm_enqueued = false;
+  b->ready = false;
   int rc;
   if ((rc = reserve_scan(b))) return bail(rc);
-  if (!same_desc(desc, b->uploaded)) {
-    if (capturing(b->stream))
-      return bail(fail(CARVE_EINVAL, "scan_batch: new image descriptors while the stream is being captured"));
+  if (upload) {
+    b->uploaded.clear();   // (until the new ones are there)
     const size_t bytes = desc.size() * sizeof(ImageDesc);
     // the staging buffer may still feed the previous upload
     if (hipStreamSynchronize(b->stream) != hipSuccess) return bail(fail(CARVE_EDEVICE, "scan_batch: sync failed"));
@@ -2329,6 +2349,7 @@ extern "C" int scan_batch(const carve_index* idx, const carve_image_desc* images
     b->uploaded = desc;
   }
   if ((rc = launch_scan(b, many_images(b)))) return bail(rc);
+  b->ready = true;
   *io = b;
   return CARVE_OK;
 }
@@ -2394,6 +2415,7 @@ extern "C" int flagged_sectors(carve_scan* sc, uint64_t* out, uint64_t cap, uint
   if (!sc || !n_out) return fail(CARVE_EINVAL, "flagged_sectors: null argument");
   if (sc->batch) return fail(CARVE_EINVAL, "flagged_sectors: a batch object (use batch_flagged_sectors)");
   if (cap && !out) return fail(CARVE_EINVAL, "flagged_sectors: null out with cap > 0");
+  CARVE_TRY(need_results(sc, "flagged_sectors"));
   uint64_t n = 0;
   if (cap && sc->n_tiles && is_device_memory(out)) {   // copy on the device, then one synchronization
     CARVE_TRY(enqueue_id_copy(sc, out, cap));
@@ -2413,6 +2435,7 @@ extern "C" int flagged_sectors_enqueue(carve_scan* sc, uint64_t* out, uint64_t c
   if (sc->batch) return fail(CARVE_EINVAL, "flagged_sectors_enqueue: a batch object");
   if (cap && !out) return fail(CARVE_EINVAL, "flagged_sectors_enqueue: null out with cap > 0");
   if (cap && !is_device_memory(out)) return fail(CARVE_EINVAL, "flagged_sectors_enqueue: out is not device memory");
+  CARVE_TRY(need_results(sc, "flagged_sectors_enqueue"));
   if (!cap || !sc->n_tiles) return CARVE_OK;
   return enqueue_id_copy(sc, out, cap);
 }
@@ -2435,6 +2458,7 @@ extern "C" int scan_wait_kernel(carve_scan* sc, void* stream) {
 
 extern "C" int scan_counts(carve_scan* sc, uint64_t* n_flagged, uint64_t* n_confirmed) {
   if (!sc || !n_flagged || !n_confirmed) return fail(CARVE_EINVAL, "scan_counts: null argument");
+  CARVE_TRY(need_results(sc, "scan_counts"));
   if (!sc->n_tiles) {   // nothing was scanned: no kernel ran
     *n_flagged = 0;
     *n_confirmed = sc->confirm_enqueued ? 0 : CARVE_NOT_CONFIRMED;
@@ -2453,6 +2477,7 @@ extern "C" int confirm_matches(const carve_index* idx, carve_scan* sc, carve_mat
   if (sc->batch) return fail(CARVE_EINVAL, "confirm_matches: a batch object (use batch_confirm_matches)");
   if (cap && !out) return fail(CARVE_EINVAL, "confirm_matches: null out with cap > 0");
   if (sc->idx != idx) return fail(CARVE_EINVAL, "confirm_matches: scan was made with another index");
+  CARVE_TRY(need_results(sc, "confirm_matches"));
   if (sc->fragments) return confirm_all(idx, sc, fragment_windows(sc), out, cap, n_out);
   return confirm_all(idx, sc, one_image(sc), out, cap, n_out);
 }
@@ -2461,6 +2486,7 @@ extern "C" int confirm_enqueue(const carve_index* idx, carve_scan* sc) {
   if (!idx || !sc) return fail(CARVE_EINVAL, "confirm_enqueue: null argument");
   if (sc->batch) return fail(CARVE_EINVAL, "confirm_enqueue: a batch object (use batch_confirm_enqueue)");
   if (sc->idx != idx) return fail(CARVE_EINVAL, "confirm_enqueue: scan was made with another index");
+  CARVE_TRY(need_results(sc, "confirm_enqueue"));
   if (sc->fragments) return confirm_enqueue_impl<FragmentWindows, carve_match>(idx, sc, fragment_windows(sc));
   return confirm_enqueue_impl<OneImage, carve_match>(idx, sc, one_image(sc));
 }
@@ -2471,6 +2497,7 @@ extern "C" int confirm_enqueue_to(const carve_index* idx, carve_scan* sc, carve_
   if (sc->idx != idx) return fail(CARVE_EINVAL, "confirm_enqueue_to: scan was made with another index");
   if (cap && !out) return fail(CARVE_EINVAL, "confirm_enqueue_to: null out with cap > 0");
   if (cap && !is_device_memory(out)) return fail(CARVE_EINVAL, "confirm_enqueue_to: out is not device memory");
+  CARVE_TRY(need_results(sc, "confirm_enqueue_to"));
   carve_match* dest = cap ? out : nullptr;
   if (sc->fragments)
     return confirm_enqueue_impl<FragmentWindows, carve_match>(idx, sc, fragment_windows(sc), dest, cap);
@@ -2480,6 +2507,7 @@ extern "C" int confirm_enqueue_to(const carve_index* idx, carve_scan* sc, carve_
 extern "C" int batch_confirm_enqueue(const carve_index* idx, carve_batch* b) {
   if (!idx || !b) return fail(CARVE_EINVAL, "batch_confirm_enqueue: null argument");
   if (b->idx != idx) return fail(CARVE_EINVAL, "batch_confirm_enqueue: batch was made with another index");
+  CARVE_TRY(need_results(b, "batch_confirm_enqueue"));
   return confirm_enqueue_impl<ManyImages, carve_batch_match>(idx, b, many_images(b));
 }
 
@@ -2494,6 +2522,7 @@ int read_img_off(carve_batch* b) {
 
 extern "C" int batch_flag_counts(carve_batch* b, uint64_t* counts, uint32_t n_images) {
   if (!b || (n_images && !counts)) return fail(CARVE_EINVAL, "batch_flag_counts: null argument");
+  CARVE_TRY(need_results(b, "batch_flag_counts"));
   if (n_images != b->n_images) return fail(CARVE_EINVAL, "batch_flag_counts: the batch has %u images", b->n_images);
   if (!n_images) return CARVE_OK;
   CARVE_TRY(read_img_off(b));
@@ -2504,6 +2533,7 @@ extern "C" int batch_flag_counts(carve_batch* b, uint64_t* counts, uint32_t n_im
 
 extern "C" int batch_flagged_sectors(carve_batch* b, uint32_t image, uint64_t* out, uint64_t cap, uint64_t* n_out) {
   if (!b || !n_out) return fail(CARVE_EINVAL, "batch_flagged_sectors: null argument");
+  CARVE_TRY(need_results(b, "batch_flagged_sectors"));
   const bool all = image == CARVE_ALL_IMAGES;
   if (!all && image >= b->n_images) return fail(CARVE_EINVAL, "batch_flagged_sectors: image %u of %u", image,
                                                 b->n_images);
@@ -2529,6 +2559,7 @@ extern "C" int batch_confirm_matches(const carve_index* idx, carve_batch* b, car
   if (!idx || !b || !n_out) return fail(CARVE_EINVAL, "batch_confirm_matches: null argument");
   if (cap && !out) return fail(CARVE_EINVAL, "batch_confirm_matches: null out with cap > 0");
   if (b->idx != idx) return fail(CARVE_EINVAL, "batch_confirm_matches: batch was made with another index");
+  CARVE_TRY(need_results(b, "batch_confirm_matches"));
   return confirm_all(idx, b, many_images(b), out, cap, n_out);
 }
 
@@ -2561,6 +2592,7 @@ CARVE_HIDDEN int carve_batch_reserve(const carve_index* idx, carve_batch** io, u
   b->n_tiles = keep_tiles;
   b->n_images = keep_images;
   if (rc != CARVE_OK) {
+    b->ready = false;
     if (created) free_batch(b);
     return rc;
   }
@@ -2573,6 +2605,7 @@ CARVE_HIDDEN int carve_batch_stage_out(carve_batch* b, int with_matches, const c
   if (!b || !st || !match_room || !st->totals || !st->img_off || (st->ids_cap && !st->ids) ||
       (st->match_cap && !st->matches))
     return fail(CARVE_EINVAL, "carve_batch_stage_out: null argument");
+  CARVE_TRY(need_results(b, "carve_batch_stage_out"));
   if (with_matches && !b->confirm_enqueued)
     return fail(CARVE_EINVAL, "carve_batch_stage_out: confirmation was not enqueued");
   // an empty tile space writes no counts: stage zeros (the offsets are zero-filled)

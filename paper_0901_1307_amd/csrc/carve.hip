@@ -1144,9 +1144,12 @@ int scan_counts(const Items& items, uint32_t* out, uint64_t n, uint64_t* d_total
 
 // A scan takes the kernels without a loop (a wave per 16 sectors, or for the CRC
 // per tile) unless its launch shape asks for something else (a cap on the grid,
-// runs of tiles), or its grid would be too large.
+// runs of tiles), or its grid would be too large: 2^26 blocks of a wave are 2^32
+// threads, which cannot be launched.
+constexpr bool grid_without_loop(uint64_t n_tiles) { return n_tiles * kTileParts < kMaxPartBlocks; }
+static_assert(grid_without_loop((1ull << 24) - 1) && !grid_without_loop(1ull << 24), "1 TiB less a tile at most");
 bool scan_without_loop(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
-  return !per_cu_cap && chunk <= 1 && n_tiles * kTileParts <= kMaxPartBlocks;
+  return !per_cu_cap && chunk <= 1 && grid_without_loop(n_tiles);
 }
 
 template <int kMode, int kSig, int kLayout, class Src>

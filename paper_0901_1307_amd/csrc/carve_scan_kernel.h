@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 // sectors a wave 1% faster on 8 GiB and up to 7% slower below 1 GiB.
 constexpr uint32_t kPart = 16;                          // sectors per wave
 constexpr uint32_t kTileParts = kTileSectors / kPart;
-constexpr uint64_t kMaxPartBlocks = 1ull << 26;         // a grid has fewer than 2^32 threads
+constexpr uint64_t kMaxPartBlocks = 1ull << 26;         // fewer: a grid has fewer than 2^32 threads
 
 // A wave's sectors `rows` (part `part` of the tile with hit word *out).
 template <int kLayout, uint32_t kSlotStride, bool kSlots, bool kFiltered, class Rows>

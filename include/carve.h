@@ -212,7 +212,8 @@ int confirm_matches(const carve_index* idx, carve_scan* sc, carve_match* out, ui
  * scan and confirm_enqueue leaves only the copy to it. Where a replay has more
  * records (or flagged windows) than the captured confirmation has room for,
  * confirm_matches produces them in other buffers: what the graph writes to
- * stays where it is.
+ * stays where it is. (A larger image scanned with the same object outside of the
+ * graph does move it: capture again after that.)
  */
 int confirm_enqueue(const carve_index* idx, carve_scan* sc);
 

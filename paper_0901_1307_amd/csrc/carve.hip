@@ -1541,7 +1541,10 @@ int reserve_scan(carve_scan* sc) {
   const uint64_t n_words = sc->n_tiles ? sc->n_tiles : 1;
   const uint64_t nb = cdiv(n_words, kItemsPerBlock);
   // a single image of sectors may be scanned split by position (k_scan_tau):
-  // its tiles of 64 clusters reach slot 512 * ceil(n_words / 8)
+  // its tiles of 64 clusters reach slot 512 * ceil(n_words / 8). There is room
+  // for that whichever way it is scanned (at most 7 tiles more), and the split
+  // scan's own words are apart, so changing from one to the other moves nothing
+  // that a captured scan of the image uses.
   const bool split = !sc->batch && !sc->fragments && sc->idx && use_split(sc->idx, sc->desc[0].any_tau, sc->n_tiles);
   const uint64_t tau_tiles = cdiv(n_words, kPositions);
   CARVE_TRY(reserve_parts(
@@ -1549,11 +1552,10 @@ int reserve_scan(carve_scan* sc) {
       {{&sc->bitmap, n_words * 8},
        {&sc->ws, 2 * nb * 8},
        {&sc->ids, n_words * kTileSectors * 8},
-       {&sc->hit_slot, (split ? tau_tiles * kPositions : n_words) * kTileSectors * 4},
+       {&sc->hit_slot, (sc->batch || sc->fragments ? n_words : tau_tiles * kPositions) * kTileSectors * 4},
        {&sc->count, 64},
        {&sc->img_of, sc->batch ? n_words * kTileSectors * 4 : 0},
        {&sc->img_off, sc->batch ? (sc->n_images + 1) * 8ull : 0}}));
-  // (apart: a scan that needs them moves nothing that a captured contiguous scan uses)
   if (split) CARVE_TRY(sc->tau_words.reserve((tau_counter_offset(n_words) + kTauCounters) * 8));
   if (sc->timing && sc->ev.empty()) CARVE_TRY(create_timing_ring(sc));
   CARVE_TRY(sc->h_count.reserve(64));

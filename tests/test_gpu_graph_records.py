@@ -105,3 +105,29 @@ def test_more_and_fewer_windows_than_room(order):
         torch.cuda.synchronize()
         assert np.array_equal(carve.flagged_sectors(state).numpy(), units)
         _check(carve.confirm_matches(idx, state), units, same)
+
+
+@pytest.mark.parametrize("n_words", [9, 16, 23])
+def test_captured_scan_beside_a_split_scan(n_words):
+    """A graph of a contiguous scan, replayed after the same object scanned the
+    image split by position (whose words are eight to a group)."""
+    masters = _random(64 * SECTOR, 5).view(64, SECTOR)
+    idx = carve.build_master_index(masters.view(-1), [0, 64])
+    n = 64 * n_words - 5
+    img = torch.zeros(n, SECTOR, dtype=torch.uint8, device="cuda")
+    at = torch.arange(0, n, 7, device="cuda")
+    img[at] = masters[at % 64]
+    state = carve.Scan()
+    g = _captured(lambda: carve.scan_image(idx, img.view(-1), tau_mode=carve.CARVE_TAU_ANY, scan=state))
+    idx.set_scan_config(0, 0, carve.CARVE_SPLIT_ON)
+    for rep in range(3):
+        carve.scan_image(idx, img.view(-1), scan=state)
+        assert np.array_equal(carve.flagged_sectors(state).numpy(), at.cpu().numpy())
+        others = [_random(1 << 20, rep) for _ in range(8)]   # takes what was freed, if anything was
+        img[at[rep]] = 0
+        at = at[at != at[rep]]
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(carve.flagged_sectors(state).numpy(), at.cpu().numpy())
+        del others

@@ -260,9 +260,7 @@ int scan_counts(carve_scan* sc, uint64_t* n_flagged, uint64_t* n_confirmed);
  * run beside them. Nothing to wait for before the first scan. An ordering
  * point only: no results are handed over (the scan's outputs are read after
  * its compaction, on its own stream), so the wait carries no system-scope
- * cache fence. The first call for a scan object waits for everything enqueued
- * on the scan's stream so far; from then on its scans mark their kernel's end.
- * For keeping several steps in flight on several streams
+ * cache fence. For keeping several steps in flight on several streams
  * (Section 3.2's pipeline of scans, with the host never waiting between
  * them).
  * Errors: EINVAL (null sc), EDEVICE.

@@ -24,6 +24,7 @@
 //   k_master_meta, k_scan_parts<kSigs> / k_frag_sigs, k_insert, k_scatter,
 //   k_sort_segments, k_bloom_build; k_occupied, k_insert_linear and a radix
 //   sort for the other layouts; k_lds_filter_build for fragments.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdarg.h>
 #include <stdint.h>
@@ -78,8 +79,8 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;   // master whose key could not be pla
 // or 0 when none did. The first two are kept on the device, where later kernels
 // read them, and all three in pinned host memory, written there by the kernels
 // that finish them: the host reads them after a synchronization with no copy
-// enqueued for it (a 64 MiB disk's step 51 -> 48 us together with the scan's
-// ordering event, below). Every scan's compaction clears the tag, so a scan
+// enqueued for it (a 64 MiB disk's step 51 -> 48 us, with the scan's ordering
+// event no longer recorded behind its kernel). Every scan's compaction clears the tag, so a scan
 // replayed from a captured graph (which runs no host code) still invalidates an
 // earlier confirmation; and a confirmation replayed from one leaves its own tag,
 // by which the host knows where that one wrote its records.
@@ -1072,10 +1073,33 @@ struct HostBuf {
 
 uint64_t cdiv(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // (the null stream cannot be captured)
+  return false;
+}
+
+// Where a scan kernel is enqueued, and the event that marks its end there (or
+// null). Given to the launch, the event is the kernel's own completion: a 64 MiB
+// disk's step takes 41.9 us, 41.6 without one and 45 with one recorded behind the
+// kernel, so every scan object's scans carry it.
+struct ScanQueue {
+  hipStream_t s;
+  hipEvent_t done;
+};
+template <class... P, class... A>
+void launch_marked(const ScanQueue& q, void (*kernel)(P...), uint64_t grid, uint32_t threads, const A&... args) {
+  if (q.done)
+    hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, q.s, nullptr, q.done, 0, (P)args...);
+  else
+    kernel<<<(unsigned)grid, threads, 0, q.s>>>(args...);
+}
+
 // One scan kernel launch for the signature kind chosen at run time.
 template <int kMode, class Src>
 int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
-                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
+                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, const ScanQueue& q,
                   uint32_t layout = CARVE_LAYOUT_BUCKETED);
 
 int device_cus() {
@@ -1154,40 +1178,40 @@ bool scan_without_loop(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
 
 template <int kMode, int kSig, int kLayout, class Src>
 void launch_k_scan_as(const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap, const IndexView& ix,
-                      uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
+                      uint64_t* out, uint32_t* hit_slot, const ScanQueue& q) {
   if (scan_without_loop(per_cu_cap, chunk, n_tiles)) {
     if constexpr (kSig == kSigDjb2)
-      k_scan_parts<kMode, Src, kLayout><<<(unsigned)(n_tiles * kTileParts), kWave, 0, s>>>(src, ix, out, hit_slot);
+      launch_marked(q, k_scan_parts<kMode, Src, kLayout>, n_tiles * kTileParts, kWave, src, ix, out, hit_slot);
     else
-      k_scan_tiles<kMode, Src, kLayout><<<(unsigned)cdiv(n_tiles, kScanWaves), kScanThreads, 0, s>>>(src, n_tiles, ix,
-                                                                                                    out, hit_slot);
+      launch_marked(q, k_scan_tiles<kMode, Src, kLayout>, cdiv(n_tiles, kScanWaves), kScanThreads, src, n_tiles, ix, out,
+                    hit_slot);
     return;
   }
   const uint64_t want = cdiv(cdiv(n_tiles, chunk), kScanWaves);
   const int grid = resident_grid(k_scan<kMode, kSig, Src, kLayout>, kScanThreads, want, per_cu_cap);
-  k_scan<kMode, kSig, Src, kLayout><<<grid, kScanThreads, 0, s>>>(src, chunk, ix, out, hit_slot);
+  launch_marked(q, k_scan<kMode, kSig, Src, kLayout>, grid, kScanThreads, src, chunk, ix, out, hit_slot);
 }
 
 template <int kMode, int kSig, class Src>
 void launch_k_scan_sig(uint32_t layout, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
-                       const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s) {
+                       const IndexView& ix, uint64_t* out, uint32_t* hit_slot, const ScanQueue& q) {
   if constexpr (kMode == kFlags || kMode == kFlagBits) {
     if (layout == CARVE_LAYOUT_LINEAR)
-      return launch_k_scan_as<kMode, kSig, kLayoutLinear>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
+      return launch_k_scan_as<kMode, kSig, kLayoutLinear>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, q);
     if (layout == CARVE_LAYOUT_SORTED)
-      return launch_k_scan_as<kMode, kSig, kLayoutSorted>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
+      return launch_k_scan_as<kMode, kSig, kLayoutSorted>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, q);
   }
-  launch_k_scan_as<kMode, kSig, kLayoutBucketed>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
+  launch_k_scan_as<kMode, kSig, kLayoutBucketed>(src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, q);
 }
 
 template <int kMode, class Src>
 int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap,
-                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, hipStream_t s,
+                  const IndexView& ix, uint64_t* out, uint32_t* hit_slot, const ScanQueue& q,
                   uint32_t layout) {
   if (kind == CARVE_SIG_CRC64_ISO)
-    launch_k_scan_sig<kMode, kSigCrc64>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
+    launch_k_scan_sig<kMode, kSigCrc64>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, q);
   else
-    launch_k_scan_sig<kMode, kSigDjb2>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, s);
+    launch_k_scan_sig<kMode, kSigDjb2>(layout, src, n_tiles, chunk, per_cu_cap, ix, out, hit_slot, q);
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }
@@ -1197,37 +1221,36 @@ int launch_k_scan(uint32_t kind, const Src& src, uint64_t n_tiles, uint32_t chun
 template <int kSig, int kLayout, bool kSlots>
 void launch_k_scan_tau_as(const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk, uint32_t per_cu_cap,
                           const IndexView& ix, uint64_t* tau_words, uint32_t* hit_slot, uint64_t* ctr,
-                          hipStream_t s) {
+                          const ScanQueue& q) {
   if (scan_without_loop(per_cu_cap, chunk, kPositions * words_per_pos)) {
     if constexpr (kSig == kSigDjb2)
-      k_scan_tau_parts<kLayout, kSlots><<<(unsigned)(kPositions * words_per_pos * kTileParts), kWave, 0, s>>>(
-          d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
+      launch_marked(q, k_scan_tau_parts<kLayout, kSlots>, kPositions * words_per_pos * kTileParts, kWave, d.base,
+                    d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
     else
-      k_scan_tau_tiles<kLayout, kSlots><<<(unsigned)(kPositions * cdiv(words_per_pos, kScanWaves)), kScanThreads, 0, s>>>(
-          d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
+      launch_marked(q, k_scan_tau_tiles<kLayout, kSlots>, kPositions * cdiv(words_per_pos, kScanWaves), kScanThreads,
+                    d.base, d.n_sectors, d.tau0, words_per_pos, ix, tau_words, hit_slot);
     return;
   }
   const uint64_t want = kPositions * cdiv(cdiv(words_per_pos, chunk), kScanWaves);
   int grid = resident_grid(k_scan_tau<kSig, kLayout, kSlots>, kScanThreads, want, per_cu_cap);
   grid = grid < (int)kPositions ? (int)kPositions : grid - grid % (int)kPositions;
-  k_fill_u64<<<1, 256, 0, s>>>(ctr, kTauCounters, 0);   // the work-sharing counters start at zero
-  k_scan_tau<kSig, kLayout, kSlots><<<grid, kScanThreads, 0, s>>>(d.base, d.n_sectors, d.tau0, words_per_pos, chunk,
-                                                                   ix, tau_words, hit_slot,
-                                                                   (unsigned int*)ctr);
+  k_fill_u64<<<1, 256, 0, q.s>>>(ctr, kTauCounters, 0);   // the work-sharing counters start at zero
+  launch_marked(q, k_scan_tau<kSig, kLayout, kSlots>, grid, kScanThreads, d.base, d.n_sectors, d.tau0, words_per_pos, chunk,
+                ix, tau_words, hit_slot, (unsigned int*)ctr);
 }
 
 template <int kSig, bool kSlots>
 void launch_k_scan_tau_sig(uint32_t layout, const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk,
                            uint32_t per_cu_cap, const IndexView& ix, uint64_t* tau_words,
-                           uint32_t* hit_slot, uint64_t* ctr, hipStream_t s) {
+                           uint32_t* hit_slot, uint64_t* ctr, const ScanQueue& q) {
   if (layout == CARVE_LAYOUT_LINEAR)
     return launch_k_scan_tau_as<kSig, kLayoutLinear, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                              hit_slot, ctr, s);
+                                                              hit_slot, ctr, q);
   if (layout == CARVE_LAYOUT_SORTED)
     return launch_k_scan_tau_as<kSig, kLayoutSorted, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                              hit_slot, ctr, s);
+                                                              hit_slot, ctr, q);
   launch_k_scan_tau_as<kSig, kLayoutBucketed, kSlots>(d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                       hit_slot, ctr, s);
+                                                       hit_slot, ctr, q);
 }
 
 // The position-split scan's work-sharing counters sit behind its hit words,
@@ -1243,18 +1266,18 @@ uint64_t* tau_counters(uint64_t* tau_words, uint64_t n_words) {
 // words, 256-byte aligned, for the work-sharing counters (cleared here).
 int launch_k_scan_tau(uint32_t kind, uint32_t layout, const ImageDesc& d, uint64_t words_per_pos, uint32_t chunk,
                       uint32_t per_cu_cap, const IndexView& ix, uint64_t* tau_words, uint32_t* hit_slot,
-                      uint64_t* ctr, hipStream_t s) {
+                      uint64_t* ctr, const ScanQueue& q) {
   const bool crc = kind == CARVE_SIG_CRC64_ISO;
   if (hit_slot) {
     if (crc) launch_k_scan_tau_sig<kSigCrc64, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                     hit_slot, ctr, s);
+                                                     hit_slot, ctr, q);
     else launch_k_scan_tau_sig<kSigDjb2, true>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                hit_slot, ctr, s);
+                                                hit_slot, ctr, q);
   } else {
     if (crc) launch_k_scan_tau_sig<kSigCrc64, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                      nullptr, ctr, s);
+                                                      nullptr, ctr, q);
     else launch_k_scan_tau_sig<kSigDjb2, false>(layout, d, words_per_pos, chunk, per_cu_cap, ix, tau_words,
-                                                 nullptr, ctr, s);
+                                                 nullptr, ctr, q);
   }
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
@@ -1352,9 +1375,7 @@ struct carve_scan {
   // timing: launch k brackets its scan kernel with ev[2 (k mod kTimedRing)]
   // and ev[2 (k mod kTimedRing) + 1]; n_timed launches so far
   std::vector<hipEvent_t> ev;
-  // recorded after each scan kernel, before the compaction, once scan_wait_kernel has been called: the
-  // record costs the stream about 4 us between the two
-  hipEvent_t kernel_done = nullptr;
+  hipEvent_t kernel_done = nullptr;   // the end of the latest scan kernel, before the compaction (scan_wait_kernel)
   bool launched = false;   // a scan kernel was enqueued
   bool ready = false;      // the latest scan was enqueued whole: false from its start on, and after one that failed
   uint64_t n_timed = 0;
@@ -1478,6 +1499,8 @@ int launch_scan(carve_scan* sc, const Src& src) {
     one = src.d;
     split = use_split(idx, one.any_tau, n_words);
   }
+  const bool in_graph = capturing(s);   // (a captured launch takes no event)
+  const ScanQueue q{s, in_graph ? nullptr : sc->kernel_done};
   const uint64_t slot = 2 * (sc->n_timed % kTimedRing);
   if (sc->timing) HIP_TRY(hipEventRecord(sc->ev[slot], s));
   if constexpr (std::is_same<Src, FragmentWindows>::value) {
@@ -1488,19 +1511,19 @@ int launch_scan(carve_scan* sc, const Src& src) {
     // no wave with more than one task: the kernel of the shorter chain
     const bool once = n_tasks <= (uint64_t)grid * kFragWaves;
     const auto kernel = !once ? loop : ix.bloom ? k_frag_scan_once<true> : k_frag_scan_once<false>;
-    kernel<<<grid, kFragThreads, 0, s>>>((const uint32_t*)src.d.base, src.d.n_sectors, sc->n_dwords, ix,
-                                         sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>());
+    launch_marked(q, kernel, grid, kFragThreads, (const uint32_t*)src.d.base, src.d.n_sectors, sc->n_dwords, ix,
+                  sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>());
     HIP_TRY(hipGetLastError());
   } else if (split) {
     const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
     CARVE_TRY(launch_k_scan_tau(idx->sig_kind, idx->layout, one, cdiv(n_words, kPositions), chunk,
                                 per_cu, idx->view(), sc->tau_words.as<uint64_t>(),
                                 sc->hit_slot.as<uint32_t>(), tau_counters(sc->tau_words.as<uint64_t>(), n_words),
-                                s));
+                                q));
   } else {
     const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
     CARVE_TRY(launch_k_scan<kFlags>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(),
-                                     sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>(), s,
+                                     sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>(), q,
                                      idx->layout));
   }
   if (sc->timing) {
@@ -1509,7 +1532,7 @@ int launch_scan(carve_scan* sc, const Src& src) {
     sc->timed = true;
   }
   sc->launched = true;
-  if (sc->kernel_done) HIP_TRY(hipEventRecord(sc->kernel_done, s));
+  if (in_graph) HIP_TRY(hipEventRecord(sc->kernel_done, s));
   const IdsOut out{sc->ids.as<uint64_t>(),
                    sc->batch ? sc->img_of.as<uint32_t>() : nullptr,
                    sc->batch ? sc->img_off.as<uint64_t>() : nullptr,
@@ -1558,6 +1581,11 @@ int reserve_scan(carve_scan* sc) {
        {&sc->img_off, sc->batch ? (sc->n_images + 1) * 8ull : 0}}));
   if (split) CARVE_TRY(sc->tau_words.reserve((tau_counter_offset(n_words) + kTauCounters) * 8));
   if (sc->timing && sc->ev.empty()) CARVE_TRY(create_timing_ring(sc));
+  // an ordering point for other streams only (no host read, no data handed
+  // over), so without the system-scope fence that writes back and invalidates
+  // the caches
+  if (!sc->kernel_done)
+    HIP_TRY(hipEventCreateWithFlags(&sc->kernel_done, hipEventDisableTiming | hipEventDisableSystemFence));
   CARVE_TRY(sc->h_count.reserve(64));
   return CARVE_OK;
 }
@@ -1574,13 +1602,6 @@ int read_flagged(carve_scan* sc, uint64_t* n) {
   CARVE_TRY(read_counts(sc, c));
   *n = c[0];
   return CARVE_OK;
-}
-
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();   // (the null stream cannot be captured)
-  return false;
 }
 
 // Confirmation buffers for up to cap_f flagged units. Records: room for
@@ -1773,7 +1794,8 @@ extern "C" int sector_signatures_kind(uint32_t sig_kind, const void* sectors, ui
   if ((uintptr_t)sectors % 16) return fail(CARVE_EINVAL, "sector_signatures: sectors not 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const OneImage src{ImageDesc{(const uint8_t*)sectors, n_sectors, 0, 0, 0}};
-  return launch_k_scan<kSigs>(sig_kind, src, cdiv(n_sectors, kTileSectors), 1, 0, IndexView{}, sigs, nullptr, s);
+  return launch_k_scan<kSigs>(sig_kind, src, cdiv(n_sectors, kTileSectors), 1, 0, IndexView{}, sigs, nullptr,
+                              ScanQueue{s, nullptr});
 }
 
 extern "C" int sector_signatures(const void* sectors, uint64_t n_sectors, uint64_t* sigs, void* stream) {
@@ -1995,7 +2017,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
       const uint64_t n_tiles = cdiv(n_masters, kTileSectors);
       const OneImage src{ImageDesc{ix->masters, n_masters, 0, 0, 0}};
       if ((rc = launch_k_scan<kSigs>(ix->sig_kind, src, n_tiles, 1, 0, IndexView{}, sig.as<uint64_t>(),
-                                     nullptr, s)))
+                                     nullptr, ScanQueue{s, nullptr})))
         return bail2(rc);
     }
     k_insert<<<nbk, 256, 0, s>>>(sig.as<uint64_t>(), n_masters, ix->keys.as<uint64_t>(), lb, extra.as<uint32_t>(),
@@ -2246,15 +2268,16 @@ extern "C" int scan_image_noalloc(const carve_index* idx, const void* image, uin
   const uint32_t per_cu = idx->cfg.blocks_per_cu;
   const uint32_t chunk = idx->cfg.tiles_per_chunk ? idx->cfg.tiles_per_chunk : 1;
   const IdsOut out{ids, nullptr, nullptr, cap, count, nullptr};
+  const ScanQueue q{s, nullptr};
   if (use_split(idx, src.d.any_tau, n_words)) {   // as scan_image: the position-split scan
     CARVE_TRY(launch_k_scan_tau(idx->sig_kind, idx->layout, src.d, cdiv(n_words, kPositions), chunk, per_cu,
-                                idx->view(), tau_words, nullptr, ctr, s));
+                                idx->view(), tau_words, nullptr, ctr, q));
     launch_ids(src, bitmap, n_words, sums, out, s,
                TauMergeItems{tau_words, cdiv(n_words, kPositions), bitmap, n_words, tau0,
                              (uint32_t)(n_sectors % kTileSectors)}, true);
   } else {
     CARVE_TRY(launch_k_scan<kFlagBits>(idx->sig_kind, src, n_words, chunk, per_cu, idx->view(), bitmap,
-                                        nullptr, s, idx->layout));
+                                        nullptr, q, idx->layout));
     launch_ids(src, bitmap, n_words, sums, out, s, PopcountItems{bitmap}, false);
   }
   HIP_TRY(hipGetLastError());
@@ -2448,15 +2471,6 @@ extern "C" int flagged_sectors_enqueue(carve_scan* sc, uint64_t* out, uint64_t c
 extern "C" int scan_wait_kernel(carve_scan* sc, void* stream) {
   if (!sc) return fail(CARVE_EINVAL, "scan_wait_kernel: null scan");
   if (!sc->launched) return CARVE_OK;   // no scan kernel enqueued yet
-  if (!sc->kernel_done) {
-    // The first call: the latest scan kernel's end was not recorded, so this
-    // wait is for all the scan's stream holds so far; later scans record it.
-    // An ordering point for other streams only (no host read, no data handed
-    // over), so without the system-scope fence that writes back and
-    // invalidates the caches at every record.
-    HIP_TRY(hipEventCreateWithFlags(&sc->kernel_done, hipEventDisableTiming | hipEventDisableSystemFence));
-    HIP_TRY(hipEventRecord(sc->kernel_done, sc->stream));
-  }
   HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, sc->kernel_done, 0));
   return CARVE_OK;
 }

@@ -1,0 +1,42 @@
+"""scan_wait_kernel from a scan object's first scan on: the other stream waits for
+the scan kernel and not for what is enqueued behind it on the scan's stream."""
+import pytest
+import torch
+
+from paper_0901_1307_amd import carve
+
+pytestmark = pytest.mark.gpu
+SECTOR = 512
+
+
+@pytest.mark.parametrize("kind", ["djb2", "crc", "split", "capped", "capped split", "runs", "batch", "windows"])
+def test_first_scan_of_an_object(kind):
+    data = torch.randint(0, 256, (64 * SECTOR,), dtype=torch.uint8, device="cuda")
+    image = torch.randint(0, 256, (8192 * SECTOR,), dtype=torch.uint8, device="cuda")
+    image[:data.numel()] = data
+    if kind == "windows":
+        idx = carve.build_fragment_index(data, [0, data.numel() // 64])
+    else:
+        idx = carve.build_master_index(data, [0, 64], sig_kind=int(kind == "crc"))
+        idx.set_scan_config(1 if "capped" in kind else 0, 2 if kind == "runs" else 0,
+                            carve.CARVE_SPLIT_ON if "split" in kind else carve.CARVE_SPLIT_OFF)
+    ours, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def scan():
+        if kind == "batch":
+            return carve.scan_batch(idx, [(image, 0, 0)])
+        return carve.scan_fragments(idx, image) if kind == "windows" else carve.scan_image(idx, image)
+
+    scan()                                   # (the code objects are loaded)
+    torch.cuda._sleep(1000)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(ours):
+        sc = scan()
+        torch.cuda._sleep(100_000_000)       # tens of milliseconds at least
+        end = torch.cuda.Event()
+        end.record()
+    carve.scan_wait_kernel(sc, other)
+    other.synchronize()
+    assert not end.query()                   # what came behind the scan is still running
+    torch.cuda.synchronize()
+    assert carve.scan_counts(sc)[0] > 0

@@ -32,6 +32,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <initializer_list>
 #include <memory>
 #include <mutex>
@@ -975,28 +976,138 @@ int fail(int code, const char* fmt, ...) {
     if (r_ != CARVE_OK) return r_; \
   } while (0)
 
+// Device blocks that the library's buffers gave up, kept for its next ones. What
+// a block costs when it comes from the driver and goes back to it differs from
+// machine to machine and from one call to the next (some MiB: mostly 10 us, now
+// and then 300, 570 for a free of 64 MiB; elsewhere most of a millisecond), and
+// an index build and the first scan with it take five and give them back when
+// they are done.
+// It holds memory, never contents. A block enters it once all work enqueued on
+// its device has ended (what freeing it waits for as well), so whoever gets it
+// may use it on any stream. Bounded: kMostHeld bytes per device, 0.2% of it, the
+// longest unused going first; given back when an allocation fails, and after
+// kKeep without use (looked at whenever a block comes or goes). Blocks under
+// kLeast are not kept: the runtime cuts those out of larger ones itself.
+class BlockStore {
+ public:
+  static constexpr size_t kLeast = 1ull << 20, kMostHeld = 512ull << 20;
+  static constexpr int kDevices = 64;
+  // A block of at least `need` bytes (and at most twice that) of device dev, or null; its size in *bytes.
+  void* take(int dev, size_t need, size_t* bytes) {
+    if (need < kLeast || dev < 0 || dev >= kDevices) return nullptr;
+    std::vector<Block> old;
+    void* p = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      std::vector<Block>& held = held_[dev];
+      size_t best = held.size();
+      for (size_t i = 0; i < held.size(); ++i)
+        if (held[i].bytes >= need && held[i].bytes <= 2 * need && (best == held.size() || held[i].bytes < held[best].bytes))
+          best = i;
+      if (best < held.size()) {
+        p = held[best].p;
+        *bytes = held[best].bytes;
+        held.erase(held.begin() + (ptrdiff_t)best);
+      }
+      expired(dev, old);
+    }
+    to_driver(old);
+    return p;
+  }
+  // Keeps p for later; false when it does not. idle: the caller has waited for all work that uses it.
+  bool give(int dev, void* p, size_t bytes, bool idle) {
+    int cur = -1;
+    if (bytes < kLeast || bytes > kMostHeld || dev < 0 || dev >= kDevices || hipGetDevice(&cur) != hipSuccess || cur != dev)
+      return false;
+    if (!idle && hipDeviceSynchronize() != hipSuccess) {   // (as while a stream is being captured)
+      (void)hipGetLastError();
+      return false;
+    }
+    std::vector<Block> old;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      expired(dev, old);
+      std::vector<Block>& held = held_[dev];   // in the order of their coming
+      size_t sum = bytes;
+      for (const Block& b : held) sum += b.bytes;
+      size_t drop = 0;
+      for (; sum > kMostHeld; ++drop) sum -= held[drop].bytes;
+      old.insert(old.end(), held.begin(), held.begin() + (ptrdiff_t)drop);
+      held.erase(held.begin(), held.begin() + (ptrdiff_t)drop);
+      held.push_back(Block{p, bytes, Clock::now()});
+    }
+    to_driver(old);
+    return true;
+  }
+  // Everything held of device dev back to the driver; whether there was anything.
+  bool trim(int dev) {
+    if (dev < 0 || dev >= kDevices) return false;
+    std::vector<Block> old;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      old.swap(held_[dev]);
+    }
+    to_driver(old);
+    return !old.empty();
+  }
+
+ private:
+  typedef std::chrono::steady_clock Clock;
+  static constexpr std::chrono::seconds kKeep{10};
+  struct Block {
+    void* p;
+    size_t bytes;
+    Clock::time_point since;
+  };
+  void expired(int dev, std::vector<Block>& out) {
+    std::vector<Block>& held = held_[dev];
+    const Clock::time_point now = Clock::now();
+    size_t n = 0;
+    while (n < held.size() && now - held[n].since > kKeep) ++n;
+    out.insert(out.end(), held.begin(), held.begin() + (ptrdiff_t)n);
+    held.erase(held.begin(), held.begin() + (ptrdiff_t)n);
+  }
+  static void to_driver(const std::vector<Block>& blocks) {
+    for (const Block& b : blocks) (void)hipFree(b.p);
+  }
+  std::mutex mu_;
+  std::vector<Block> held_[kDevices];
+};
+BlockStore& block_store() {
+  static BlockStore* store = new BlockStore();   // never destroyed: buffers may outlive the library's statics
+  return *store;
+}
+
 // Device buffer that grows on demand (contents not preserved), or a part of
 // another one (carve_up).
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   bool part = false;
+  int dev = -1;
   int reserve(size_t need) {
     if (need <= bytes) return CARVE_OK;
     release();
     size_t sz = need < 256 ? 256 : need;
-    if (hipMalloc(&p, sz) != hipSuccess) {
-      p = nullptr;
-      (void)hipGetLastError();   // reported here, not by the caller's next launch
-      return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    p = block_store().take(dev, sz, &sz);
+    if (!p) {
+      hipError_t e = hipMalloc(&p, sz);
+      if (e != hipSuccess && block_store().trim(dev)) e = hipMalloc(&p, sz);
+      if (e != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();   // reported here, not by the caller's next launch
+        return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
+      }
     }
     bytes = sz;
     return CARVE_OK;
   }
   template <class T>
   T* as() const { return (T*)p; }
-  void release() {
-    if (p && !part) (void)hipFree(p);
+  // idle: the caller has waited for all work that uses it
+  void release(bool idle = false) {
+    if (p && !part && !block_store().give(dev, p, bytes, idle)) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
     part = false;
@@ -1004,10 +1115,12 @@ struct DevBuf {
 };
 
 // One allocation for several buffers of known sizes, which become its parts (on
-// 256-byte boundaries). An allocation or a free of some MiB costs 30-300 us of
-// host time, so an index is built with three (what it keeps, its filters, what
-// only the build uses) rather than fifteen: build and first scan of 1M masters
-// 1545 -> 880 us. The parts are released before or after `whole`, no matter.
+// 256-byte boundaries): an index is built with three (what it keeps, its
+// filters, what only the build uses) rather than fifteen. Build and first scan of
+// 1M masters (median of 60, the largest after the first): fifteen from the driver
+// 1,850 us (3,300), three 920 (1,400; on another machine 3,090, spread over 80%),
+// three from the block store 547 (640, once 1,030). The parts are released before or after
+// `whole`, no matter.
 struct PartSize {
   DevBuf* buf;
   size_t need;
@@ -2092,7 +2205,10 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
         rc = carve_up(ix->filters, {{&ix->bloom, 8ull << lw}});
       }
       if (rc) return bail2(rc);
-      if (hipMemsetAsync(ix->filters.p, 0, ix->filters.bytes, s) != hipSuccess)
+      const size_t filters_end = unit == kSectorBytes ? (size_t)(ix->bloom_tau.as<uint8_t>() - ix->bloom.as<uint8_t>()) +
+                                                            ix->bloom_tau.bytes
+                                                      : ix->bloom.bytes;
+      if (hipMemsetAsync(ix->bloom.p, 0, filters_end, s) != hipSuccess)
         return bail2(fail(CARVE_EDEVICE, "build_master_index: bloom memset failed"));
       if (unit == kFragBytes)   // the same bytes as 2^(lw+1) words of 32 bits, 3 bits per signature
         k_frag_bloom_build<<<cdiv(ix->n_slots, 256), 256, 0, s>>>(ix->keys.as<uint64_t>(), ix->n_slots, lw + 1,
@@ -2121,7 +2237,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
       return bail2(fail(CARVE_EDEVICE, "build_fragment_index: filter build failed"));
   }
-  work.release();
+  work.release(true);   // (the stream was waited for after its last use)
   *out = ix;
   return CARVE_OK;
 }

@@ -1665,7 +1665,8 @@ int launch_scan(carve_scan* sc, const Src& src) {
     split = use_split(idx, one.any_tau, n_words);
   }
   const bool in_graph = capturing(s);   // (a captured launch takes no event)
-  const ScanQueue q{s, in_graph ? nullptr : sc->kernel_done};
+  const bool record = in_graph || sc->timing;   // (nor a timed one, so that its own events are next to the kernel)
+  const ScanQueue q{s, record ? nullptr : sc->kernel_done};
   const uint64_t slot = 2 * (sc->n_timed % kTimedRing);
   if (sc->timing) HIP_TRY(hipEventRecord(sc->ev[slot], s));
   if constexpr (std::is_same<Src, FragmentWindows>::value) {
@@ -1697,7 +1698,7 @@ int launch_scan(carve_scan* sc, const Src& src) {
     sc->timed = true;
   }
   sc->launched = true;
-  if (in_graph) HIP_TRY(hipEventRecord(sc->kernel_done, s));
+  if (record) HIP_TRY(hipEventRecord(sc->kernel_done, s));
   const IdsOut out{sc->ids.as<uint64_t>(),
                    sc->batch ? sc->img_of.as<uint32_t>() : nullptr,
                    sc->batch ? sc->img_off.as<uint64_t>() : nullptr,

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 SECTOR = 512
 
 
-@pytest.mark.parametrize("kind", ["djb2", "crc", "split", "capped", "capped split", "runs", "batch", "windows"])
+@pytest.mark.parametrize("kind", ["djb2", "crc", "split", "capped", "capped split", "runs", "batch", "windows", "timed"])
 def test_first_scan_of_an_object(kind):
     data = torch.randint(0, 256, (64 * SECTOR,), dtype=torch.uint8, device="cuda")
     image = torch.randint(0, 256, (8192 * SECTOR,), dtype=torch.uint8, device="cuda")
@@ -25,6 +25,10 @@ def test_first_scan_of_an_object(kind):
     def scan():
         if kind == "batch":
             return carve.scan_batch(idx, [(image, 0, 0)])
+        if kind == "timed":   # (the object's second scan: timing is switched on for an object that there is)
+            sc = carve.scan_image(idx, image)
+            sc.set_timing(True)
+            return carve.scan_image(idx, image, scan=sc)
         return carve.scan_fragments(idx, image) if kind == "windows" else carve.scan_image(idx, image)
 
     scan()                                   # (the code objects are loaded)

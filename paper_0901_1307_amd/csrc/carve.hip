@@ -1352,9 +1352,11 @@ void launch_k_scan_as(const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t
                     hit_slot);
     return;
   }
-  const uint64_t want = cdiv(cdiv(n_tiles, chunk), kScanWaves);
-  const int grid = resident_grid(k_scan<kMode, kSig, Src, kLayout>, kScanThreads, want, per_cu_cap);
-  launch_marked(q, k_scan<kMode, kSig, Src, kLayout>, grid, kScanThreads, src, chunk, ix, out, hit_slot);
+  auto kernel = k_scan<kMode, kSig, Src, kLayout, false>;
+  if constexpr (kMode != kSigs && kLayout == kLayoutBucketed)
+    if (ix.bloom) kernel = k_scan<kMode, kSig, Src, kLayout, true>;
+  const int grid = resident_grid(kernel, kScanThreads, cdiv(cdiv(n_tiles, chunk), kScanWaves), per_cu_cap);
+  launch_marked(q, kernel, grid, kScanThreads, src, chunk, ix, out, hit_slot);
 }
 
 template <int kMode, int kSig, class Src>
@@ -2558,7 +2560,7 @@ CARVE_HIDDEN int carve_batch_set_grid(carve_batch* b, uint32_t blocks_per_cu) {
 }
 
 CARVE_HIDDEN uint32_t carve_batch_scan_blocks_per_cu(void) {
-  return (uint32_t)blocks_per_cu(k_scan<kFlags, kSigDjb2, ManyImages, kLayoutBucketed>, kScanThreads);
+  return (uint32_t)blocks_per_cu(k_scan<kFlags, kSigDjb2, ManyImages, kLayoutBucketed, true>, kScanThreads);
 }
 
 extern "C" int scan_set_timing(carve_scan* sc, int enable) {

@@ -113,14 +113,21 @@ struct ManyImages {
 template <int kSig>
 struct TileHash {
   Djb2Lane d;
-  __device__ __forceinline__ explicit TileHash(uint32_t) { load_djb2_lane(d); }
+  uint32_t first;   // the sixteen sectors it begins a tile with
+  __device__ __forceinline__ explicit TileHash(uint32_t wave) : first(wave % (kTileSectors / 16)) { load_djb2_lane(d); }
   template <class Rows>
   __device__ __forceinline__ void load(const Rows& rows, PhaseRegs& r) const {   // a tile's first phase
-    load_sectors<true>(rows, 0, r);
+    load_sectors<true>(rows, first, r);
+  }
+  // The weights again, for a kernel that needs their registers between tiles.
+  __device__ __forceinline__ void reload() {
+    uint32_t l = lane_id();
+    asm volatile("" : "+v"(l));   // (or the compiler keeps the first ones)
+    load_djb2_lane(d, l);
   }
   template <class Rows, class Prefetch>
   __device__ __forceinline__ uint64_t tile(const Rows& rows, PhaseRegs& A, PhaseRegs& B, Prefetch&& prefetch) const {
-    return tile_djb2_pipelined<true>(rows, d, A, B, prefetch);
+    return tile_djb2_pipelined<true>(rows, d, first, A, B, prefetch);
   }
 };
 template <>
@@ -134,6 +141,7 @@ struct TileHash<kSigCrc64> {
   __device__ __forceinline__ void load(const Rows& rows, PhaseRegs& r) const {
     load_phase<true>(rows, 0, r);
   }
+  __device__ __forceinline__ void reload() {}
   template <class Rows, class Prefetch>
   __device__ __forceinline__ uint64_t tile(const Rows& rows, PhaseRegs& A, PhaseRegs& B, Prefetch&& prefetch) const {
     return tile_crc_pipelined<true>(rows, my, A, B, prefetch);
@@ -145,8 +153,12 @@ struct TileHash<kSigCrc64> {
 // ask for runs of tiles): wave q takes chunks q, q + W, ... of
 // `chunk` consecutive tiles (W = waves in the grid). 4 waves per SIMD (at
 // most 128 VGPRs): the more waves, the more sector loads in flight per CU.
-// kLayout: the index's probe layout (kFlags only).
-template <int kMode, int kSig, class Src, int kLayout = kLayoutBucketed>
+// kLayout: the index's probe layout (not for kSigs). kFiltered: the index has a
+// filter. Its instance is free of the registers that the probe without one needs
+// (with those and the djb2 weights it spilled 6: 256 MiB at 4 blocks a CU 57.3 us,
+// now 46.4), and the instance without reads the weights again for each tile
+// (65.0 -> 59.0).
+template <int kMode, int kSig, class Src, int kLayout, bool kFiltered>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan(
     Src src, uint32_t chunk, IndexView ix, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
   // the wave's index, uniform (so tile addresses stay in scalar registers)
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
     const uint64_t h = hash.tile(ContiguousRows{tr.base, tr.n_valid}, A, B, prefetch);
     if constexpr (kMode == kFlags || kMode == kFlagBits) {
       const uint32_t tau = (tr.tau_first + l) & (kClusterSectors - 1);
-      uint64_t hits = tile_probe<kLayout, 1, kMode == kFlags>(
+      uint64_t hits = tile_probe<kLayout, 1, kMode == kFlags, kFiltered>(
           ix, h, tau, tr.any_tau != 0, kMode == kFlags ? hit_slot + g * kTileSectors : nullptr, ix.bloom,
           ix.log2_bloom_words);
       if (tr.n_valid < kTileSectors) hits &= (1ull << tr.n_valid) - 1ull;
@@ -191,6 +203,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
       if (l < tr.n_valid) out[g * kTileSectors + l] = h;   // one image: tile g holds sectors 64g..
     }
     if (!more) break;
+    if constexpr (kMode != kSigs && kLayout == kLayoutBucketed && !kFiltered) hash.reload();
     g = gn;
     cur = cur_n;
     tr = tn;

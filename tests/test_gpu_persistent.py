@@ -1,0 +1,46 @@
+"""The persistent scan kernels with several tiles per wave, with and without a
+filter: one image, a batch of uneven images and the call without allocation,
+against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import assert_same_matches, gpu_flags_and_matches, oracle_flags_and_matches
+from paper_0901_1307_amd import carve
+
+pytestmark = pytest.mark.gpu
+SECTOR = 512
+
+
+@pytest.mark.parametrize("kind", [carve.CARVE_SIG_DJB2_64, carve.CARVE_SIG_CRC64_ISO])
+@pytest.mark.parametrize("bloom", [0, carve.CARVE_BLOOM_OFF])
+@pytest.mark.parametrize("shape", [(0, 64), (1, 3), (4, 5)])
+def test_runs_of_tiles(shape, bloom, kind):
+    rng = np.random.default_rng(shape[1])
+    masters = rng.integers(0, 256, (700, SECTOR), dtype=np.uint8)
+    masters[33], masters[650] = 0, 255
+    offsets = [0, 300, 301, 700]
+    n = 64 * 50 + 29
+    image = rng.integers(0, 256, (n, SECTOR), dtype=np.uint8)
+    for j in {0, n - 1, *range(0, n, 9)}:
+        image[j] = masters[int(rng.integers(0, 700))]
+    idx = carve.build_master_index(torch.from_numpy(masters).reshape(-1).cuda(), offsets, sig_kind=kind,
+                                   bloom_bits_per_key=bloom)
+    idx.set_scan_config(*shape, carve.CARVE_SPLIT_OFF)
+    dev = torch.from_numpy(image).reshape(-1).cuda()
+    for tau0, any_tau in ((3, False), (0, True)):
+        want_flags, want = oracle_flags_and_matches(masters, offsets, image.reshape(-1), tau0, any_tau, sig_kind=kind)
+        flags, matches, _ = gpu_flags_and_matches(idx, dev, tau0, any_tau)
+        assert np.array_equal(flags, want_flags)
+        assert_same_matches(matches, want)
+        ids = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+        count = torch.zeros(1, dtype=torch.int64, device="cuda")
+        carve.scan_image_noalloc(idx, dev, ids, count, tau0, int(any_tau))
+        assert np.array_equal(ids[:int(count)].cpu().numpy().astype(np.uint64), want_flags)
+        cuts = [0, 8, 72, 72, 1000, 1008, 3200, n]   # pieces that keep the cluster positions
+        b = carve.scan_batch(idx, [(dev[a * SECTOR:e * SECTOR], tau0, int(any_tau)) for a, e in zip(cuts, cuts[1:])])
+        got = [carve.batch_flagged_sectors(b, i).numpy() + a for i, a in enumerate(cuts[:-1])]
+        assert np.array_equal(np.concatenate(got).astype(np.uint64), want_flags)
+        rec = carve.batch_confirm_matches(idx, b)
+        rec["disk_sector"] += np.array(cuts, dtype=np.uint64)[rec["image"]]
+        assert_same_matches(rec[list(want.dtype.names)], want)

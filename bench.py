@@ -884,7 +884,7 @@ def run_fragments(args):
         "windows_per_s": round(n_windows / (ms_per_step * 1e-3)),
         "steps_in_flight": inflight, "ms_per_step_one_in_flight": serial,
         "flagged": n_flag, "confirmed": n_match,
-        "roofline": {"bound": "hbm", "kernel": "k_frag_scan (signatures on the matrix units + filter/table probe)",
+        "roofline": {"bound": "hbm", "kernel": "k_frag_scan (rolling signatures + filter/table probe)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel_ms": round(k_avg, 4),
                      # the kernel alone: the same kernel in the steps run one at a time

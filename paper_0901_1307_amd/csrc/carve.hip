@@ -11,7 +11,7 @@
 //                     index probe (bucketed, linear or sorted layout, Bloom
 //                     prefilter) -> one 64-bit hit word per tile (ballot); the
 //                     matched slot of each flagged sector is recorded
-//                     (carve_scan_kernel.h; k_frag_scan, k_frag_scan_once in
+//                     (carve_scan_kernel.h; k_frag_scan in
 //                     carve_fragment_kernel.h for fragments)
 //   k_reduce, k_emit_ids   chunk sums of the hit words, then ascending flagged
 //                     ids (per image, image order) and, for batches, where
@@ -1674,11 +1674,8 @@ int launch_scan(carve_scan* sc, const Src& src) {
   if constexpr (std::is_same<Src, FragmentWindows>::value) {
     const uint64_t n_tasks = cdiv(src.d.n_sectors, kWaveWindows);
     const IndexView ix = idx->view();
-    const auto loop = ix.bloom ? k_frag_scan<true> : k_frag_scan<false>;
-    const int grid = resident_grid(loop, kFragThreads, cdiv(n_tasks, kFragWaves), per_cu);
-    // no wave with more than one task: the kernel of the shorter chain
-    const bool once = n_tasks <= (uint64_t)grid * kFragWaves;
-    const auto kernel = !once ? loop : ix.bloom ? k_frag_scan_once<true> : k_frag_scan_once<false>;
+    const auto kernel = ix.bloom ? k_frag_scan<true> : k_frag_scan<false>;
+    const int grid = resident_grid(kernel, kFragThreads, cdiv(n_tasks, kFragWaves), per_cu);
     launch_marked(q, kernel, grid, kFragThreads, (const uint32_t*)src.d.base, src.d.n_sectors, sc->n_dwords, ix,
                   sc->bitmap.as<uint64_t>(), sc->hit_slot.as<uint32_t>());
     HIP_TRY(hipGetLastError());
@@ -2280,7 +2277,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     // the distinct signatures counted above include signature 0, which has no slot
     if ((rc = build_layout(ix, p, h_unique - (zmask ? 1 : 0), s))) return bail2(rc);
   }
-  if (unit == kFragBytes) {   // first-level filter: about 16 bits per signature, 1-150 KiB (always present)
+  if (unit == kFragBytes) {   // first-level filter: about 16 bits per signature, 1-160 KiB (always present)
     const uint64_t want = cdiv(16 * h_unique, 32 * 256) * 256;   // words
     const uint32_t lw = (uint32_t)(want < 256 ? 256 : (want > kLdsFilterMaxWords ? kLdsFilterMaxWords : want));
     if ((rc = ix->lds_filter.reserve(4ull * lw))) return bail2(rc);

@@ -27,6 +27,7 @@
 namespace carve {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_dw __attribute__((ext_vector_type(4), aligned(4)));   // from 4-byte boundaries
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kSectorBytes = 512;

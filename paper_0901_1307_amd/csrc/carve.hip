@@ -81,10 +81,10 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;   // master whose key could not be pla
 // read them, and all three in pinned host memory, written there by the kernels
 // that finish them: the host reads them after a synchronization with no copy
 // enqueued for it (a 64 MiB disk's step 51 -> 48 us, with the scan's ordering
-// event no longer recorded behind its kernel). Every scan's compaction clears the tag, so a scan
-// replayed from a captured graph (which runs no host code) still invalidates an
-// earlier confirmation; and a confirmation replayed from one leaves its own tag,
-// by which the host knows where that one wrote its records.
+// event no longer recorded behind its kernel). Every scan's compaction clears the
+// tag, so a scan replayed from a captured graph (which runs no host code) still
+// invalidates an earlier confirmation; and a confirmation replayed from one leaves
+// its own tag, by which the host knows where that one wrote its records.
 constexpr uint32_t kConfirmedWord = 2;
 
 // Timed launches whose kernel durations a scan object keeps (the most recent).
@@ -140,45 +140,33 @@ struct TauMergeItems {
   }
 };
 
-// Items are taken in chunks of kItemsPerBlock, chunk c = items [c kItemsPerBlock,
-// (c + 1) kItemsPerBlock); a block handles chunks blockIdx.x, + gridDim.x, ...
-// so a grid sized for a count read on the device need not cover its upper
-// bound. Chunks past the count are not touched (their sums are not scanned).
-// Within a chunk, consecutive threads take consecutive items (the sum does not
-// depend on the order), so every load instruction is coalesced. kItems: items
-// per thread, for chunks of another size than kItemsPerBlock.
+// Sums of chunks of kBlockThreads * kItems items, a block each. Consecutive
+// threads take consecutive items (the sum does not depend on the order), so every
+// load instruction is coalesced.
 template <class Items, int kItems = kItemsPerThread>
-__global__ __launch_bounds__(kBlockThreads) void k_reduce(Items items, Count count, uint64_t* __restrict__ blk_sums) {
+__global__ __launch_bounds__(kBlockThreads) void k_reduce(Items items, uint64_t n, uint64_t* __restrict__ blk_sums) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
-  constexpr uint64_t kChunk = (uint64_t)kBlockThreads * kItems;
-  const uint64_t n = count.get();
-  for (uint64_t c = blockIdx.x; c * kChunk < n; c += gridDim.x) {
-    const uint64_t base = c * kChunk + threadIdx.x;
-    uint64_t s = 0;
+  const uint64_t base = (uint64_t)blockIdx.x * kBlockThreads * kItems + threadIdx.x;
+  uint64_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const uint64_t i = base + (uint64_t)k * kBlockThreads;
-      if (i < n) s += items(i);
-    }
-    uint64_t total;
-    block_exclusive_scan<kBlockThreads>(s, lds_w, &total);
-    if (threadIdx.x == 0) blk_sums[c] = total;
+  for (int k = 0; k < kItems; ++k) {
+    const uint64_t i = base + (uint64_t)k * kBlockThreads;
+    if (i < n) s += items(i);
   }
+  uint64_t total;
+  block_exclusive_scan<kBlockThreads>(s, lds_w, &total);
+  if (threadIdx.x == 0) blk_sums[blockIdx.x] = total;
 }
 
-// One block: exclusive offsets of the block sums (chunks of `chunk` items);
-// total into *total. Only the blocks that hold items are scanned (a count read
-// on the device can be far below the capacity the launches were sized for).
+// One block: exclusive offsets of the n_blk chunk sums; total into *total.
 // Each thread takes a run of kScanRun consecutive sums per pass, its loads issued
 // together, so a pass of 4096 sums costs one memory round trip (a pass of 256,
 // one sum per thread, made the 8192 sums of a 2 GiB fragment image 23 us).
 constexpr int kScanRun = 16;
-__global__ __launch_bounds__(kBlockThreads) void k_scan_blocks(const uint64_t* __restrict__ blk_sums, Count items,
+__global__ __launch_bounds__(kBlockThreads) void k_scan_blocks(const uint64_t* __restrict__ blk_sums, uint64_t n_blk,
                                                               uint64_t* __restrict__ blk_off,
-                                                              uint64_t* __restrict__ total,
-                                                              uint64_t chunk = kItemsPerBlock) {
+                                                              uint64_t* __restrict__ total) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
-  const uint64_t n_blk = (items.get() + chunk - 1) / chunk;
   uint64_t carry = 0;
   for (uint64_t b0 = 0; b0 < n_blk; b0 += (uint64_t)kBlockThreads * kScanRun) {
     const uint64_t first = b0 + (uint64_t)threadIdx.x * kScanRun;
@@ -319,18 +307,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_emit_ids(Src src, const uint6
     }
   }
 }
-// Counts -> exclusive offsets (out[n] = total), the low 32 bits of both.
-template <class Items>
-struct EmitOffsets {
-  static constexpr bool kDenseOut = true;   // out[i] for every item i: k_apply stores it coalesced
-  Items items;
-  uint32_t* out;
-  __device__ __forceinline__ uint64_t load(uint64_t i) const { return items(i); }
-  __device__ __forceinline__ uint64_t count_of(uint64_t x) const { return x; }
-  __device__ __forceinline__ void emit(uint64_t i, uint64_t, uint64_t pos) const { out[i] = (uint32_t)pos; }
-  __device__ __forceinline__ void finish(uint64_t n, uint64_t end) const { out[n] = (uint32_t)end; }
-};
-
 // A chunk's items go through LDS: loaded coalesced (consecutive threads,
 // consecutive items), then each thread takes its kItemsPerThread consecutive
 // items for the ordered scan. One pad word per 32 spreads a thread's reads
@@ -338,66 +314,43 @@ struct EmitOffsets {
 __device__ __forceinline__ uint32_t stage_index(uint32_t j) { return j + (j >> 5); }
 constexpr uint32_t kStageWords = kItemsPerBlock + kItemsPerBlock / 32;
 
-// Items' exclusive offsets (chunks as in k_reduce). An Emit type gives an item's
-// raw value (load), its count (count_of; 0 for the value 0) and what to write
-// for it at its exclusive position (emit); finish(n, end) runs once, with end =
-// the total.
-template <class Emit>
-__global__ __launch_bounds__(kBlockThreads) void k_apply(Emit e, Count count, const uint64_t* __restrict__ blk_off) {
+// Exclusive offsets of n > 0 counts (out[n] = total), the low 32 bits of all:
+// chunks as in k_reduce, from their offsets.
+template <class Items>
+__global__ __launch_bounds__(kBlockThreads) void k_offsets(Items items, uint64_t n,
+                                                          const uint64_t* __restrict__ blk_off,
+                                                          uint32_t* __restrict__ out) {
   __shared__ uint64_t lds_w[kBlockThreads / kWave];
   __shared__ uint64_t stage[kStageWords];
-  const uint64_t n = count.get();
-  if (n == 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) e.finish(0, 0);
-    return;
+  const uint64_t c0 = (uint64_t)blockIdx.x * kItemsPerBlock;
+#pragma unroll
+  for (int k = 0; k < kItemsPerThread; ++k) {
+    const uint32_t j = (uint32_t)k * kBlockThreads + threadIdx.x;
+    stage[stage_index(j)] = c0 + j < n ? items(c0 + j) : 0;
   }
-  for (uint64_t ch = blockIdx.x; ch * kItemsPerBlock < n; ch += gridDim.x) {
-    const uint64_t c0 = ch * kItemsPerBlock;
+  __syncthreads();
+  const uint32_t j0 = threadIdx.x * kItemsPerThread;
+  uint64_t c[kItemsPerThread], s = 0;
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-      const uint32_t j = (uint32_t)k * kBlockThreads + threadIdx.x;
-      stage[stage_index(j)] = c0 + j < n ? e.load(c0 + j) : 0;
-    }
-    __syncthreads();
-    const uint32_t j0 = threadIdx.x * kItemsPerThread;
-    uint64_t x[kItemsPerThread], c[kItemsPerThread];
-    uint64_t s = 0;
+  for (int k = 0; k < kItemsPerThread; ++k) {
+    c[k] = stage[stage_index(j0 + k)];
+    s += c[k];
+  }
+  // the positions go back through LDS (every thread has read its items: the
+  // scan's barriers) and out in item order
+  uint64_t total;
+  uint64_t pos = blk_off[blockIdx.x] + block_exclusive_scan<kBlockThreads>(s, lds_w, &total);
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-      x[k] = stage[stage_index(j0 + k)];
-      c[k] = e.count_of(x[k]);
-      s += c[k];
-    }
-    // (the scan's barriers also keep the next chunk's stores behind these reads)
-    uint64_t total;
-    uint64_t pos = blk_off[ch] + block_exclusive_scan<kBlockThreads>(s, lds_w, &total);
-    if constexpr (Emit::kDenseOut) {
-      // one output per item: the positions go back through LDS (every thread
-      // has read its items: the scan's barriers) and out in item order
+  for (int k = 0; k < kItemsPerThread; ++k) {
+    stage[stage_index(j0 + k)] = pos;
+    pos += c[k];
+    if (c0 + j0 + k == n - 1) out[n] = (uint32_t)pos;
+  }
+  __syncthreads();
 #pragma unroll
-      for (int k = 0; k < kItemsPerThread; ++k) {
-        stage[stage_index(j0 + k)] = pos;
-        if (c0 + j0 + k == n - 1) e.finish(n, pos + c[k]);
-        pos += c[k];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kItemsPerThread; ++k) {
-        const uint32_t j = (uint32_t)k * kBlockThreads + threadIdx.x;
-        if (c0 + j < n) e.emit(c0 + j, 0, stage[stage_index(j)]);
-      }
-      __syncthreads();   // before the next chunk's loads overwrite the stage
-    } else {
-#pragma unroll
-      for (int k = 0; k < kItemsPerThread; ++k) {
-        const uint64_t i = c0 + j0 + k;
-        if (i < n) {
-          e.emit(i, x[k], pos);
-          pos += c[k];
-          if (i == n - 1) e.finish(n, pos);
-        }
-      }
-    }
+  for (int k = 0; k < kItemsPerThread; ++k) {
+    const uint32_t j = (uint32_t)k * kBlockThreads + threadIdx.x;
+    if (c0 + j < n) out[c0 + j] = (uint32_t)stage[stage_index(j)];
   }
 }
 
@@ -1316,17 +1269,17 @@ int resident_grid(Kernel kernel, int threads, uint64_t want, uint32_t per_cu_cap
   return (int)(want < cap ? (want ? want : 1) : cap);
 }
 
-// Exclusive scan of n counts into out[0..n] (out[n] = total); total also left in
+// Exclusive scan of n > 0 counts into out[0..n] (out[n] = total); total also left in
 // *d_total. ws holds the block sums and offsets.
 template <class Items>
 int scan_counts(const Items& items, uint32_t* out, uint64_t n, uint64_t* d_total, DevBuf& ws, hipStream_t s) {
-  const uint64_t nb = cdiv(n ? n : 1, kItemsPerBlock);
+  const uint64_t nb = cdiv(n, kItemsPerBlock);
   CARVE_TRY(ws.reserve(2 * nb * sizeof(uint64_t)));
   uint64_t* sums = ws.as<uint64_t>();
   uint64_t* offs = sums + nb;
-  k_reduce<<<nb, kBlockThreads, 0, s>>>(items, Count{n, nullptr}, sums);
-  k_scan_blocks<<<1, kBlockThreads, 0, s>>>(sums, Count{n, nullptr}, offs, d_total);
-  k_apply<<<nb, kBlockThreads, 0, s>>>(EmitOffsets<Items>{items, out}, Count{n, nullptr}, offs);   // also out[n]
+  k_reduce<<<nb, kBlockThreads, 0, s>>>(items, n, sums);
+  k_scan_blocks<<<1, kBlockThreads, 0, s>>>(sums, nb, offs, d_total);
+  k_offsets<<<nb, kBlockThreads, 0, s>>>(items, n, offs, out);   // also out[n]
   HIP_TRY(hipGetLastError());
   return CARVE_OK;
 }
@@ -1629,19 +1582,18 @@ void launch_ids(const Src& src, const uint64_t* words, uint64_t n, uint64_t* ws,
     k_emit_ids<Src, 1, true><<<cdiv(n, kBlockThreads), kBlockThreads, 0, s>>>(src, words, n, nullptr, 0, out);
     return;
   }
-  const Count count{n, nullptr};
   uint64_t nb = cdiv(n, kItemsPerBlock);
   if (nb <= kSummedChunks) {
-    k_reduce<Items><<<nb, kBlockThreads, 0, s>>>(items, count, ws);
+    k_reduce<Items><<<nb, kBlockThreads, 0, s>>>(items, n, ws);
     k_emit_ids<Src, kItemsPerThread, false><<<nb, kBlockThreads, 0, s>>>(src, words, n, ws, 0, out);
     return;
   }
   constexpr int kWide = 16;
   nb = cdiv(n, (uint64_t)kBlockThreads * kWide);
-  k_reduce<Items, kWide><<<nb, kBlockThreads, 0, s>>>(items, count, ws);
+  k_reduce<Items, kWide><<<nb, kBlockThreads, 0, s>>>(items, n, ws);
   const bool scanned = nb > kSummedChunks;
   if (scanned)
-    k_scan_blocks<<<1, kBlockThreads, 0, s>>>(ws, count, ws + nb, out.total, (uint64_t)kBlockThreads * kWide);
+    k_scan_blocks<<<1, kBlockThreads, 0, s>>>(ws, nb, ws + nb, out.total);
   k_emit_ids<Src, kWide, false><<<nb, kBlockThreads, 0, s>>>(src, words, n, scanned ? ws + nb : ws, scanned, out);
 }
 

@@ -380,7 +380,7 @@ int scan_image_noalloc(const carve_index* idx, const void* image, uint64_t n_byt
 /*
  * read_ceiling_probe -- the streaming-read rate the scan kernels are measured
  * against: one kernel reads the whole sectors of a device image once with a
- * scan kernel's access pattern (64-sector tiles, 16 B per lane with
+ * persistent scan kernel's access pattern (64-sector tiles, 16 B per lane with
  * non-temporal loads, two phases of a tile in flight, a resident grid) and no
  * other work. Not a step of the method; a measurement of the chip.
  *   pattern        0: contiguous tiles (as the contiguous scan); 1: split by
@@ -459,7 +459,7 @@ int autotune_index(const void* master_sectors, const uint64_t* file_sector_offse
                    uint64_t n_bytes, void* stream, carve_index** out, carve_tune_result* result);
 
 /*
- * scan_batch -- scan_image over n_images images at once: one persistent
+ * scan_batch -- scan_image over n_images images at once: one
  * launch over all their sectors, flags compacted per image (the paper scans
  * several disks at once, Section 3). Asynchronous on `stream`.
  *   images   host array of n_images descriptors (images BORROWED as in scan_image).

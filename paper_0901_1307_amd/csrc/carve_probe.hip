@@ -1,9 +1,11 @@
 // The streaming-read ceiling the scan kernels are priced against: a kernel
-// that reads an image once with a scan kernel's access pattern (the same
-// tiles, 16 B per lane with non-temporal loads, eight lanes per 128-byte line,
-// two phases of a tile in flight, a resident persistent grid) and does no
-// other work than folding the bytes into one register, so that what it
-// reaches is what HBM delivers to that pattern on this chip.
+// that reads an image once and does no other work than folding the bytes into
+// one register. Its pattern is that of a persistent scan for the CRC: tiles of 64
+// sectors, 16 B per lane with non-temporal loads, eight lanes per 128-byte line,
+// two phases of a tile in flight, a resident grid. The default djb2 scans read
+// otherwise (a wave per 16 sectors and no loop, four lanes per 64 bytes), so for
+// them it is what HBM delivers to a streaming read on this chip, not a bound of
+// their own pattern.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -996,27 +996,28 @@ int fail(int code, const char* fmt, ...) {
 class BlockStore {
  public:
   static constexpr size_t kLeast = 1ull << 20, kMostHeld = 512ull << 20;
-  static constexpr int kDevices = 64;
+  static constexpr int kDevices = 64, kMostBlocks = 64;
   // A block of at least `need` bytes (and at most twice that) of device dev, or null; its size in *bytes.
   void* take(int dev, size_t need, size_t* bytes) {
     if (need < kLeast || dev < 0 || dev >= kDevices) return nullptr;
-    std::vector<Block> old;
+    Blocks old;
     void* p = nullptr;
     {
       std::lock_guard<std::mutex> lock(mu_);
-      std::vector<Block>& held = held_[dev];
-      size_t best = held.size();
-      for (size_t i = 0; i < held.size(); ++i)
-        if (held[i].bytes >= need && held[i].bytes <= 2 * need && (best == held.size() || held[i].bytes < held[best].bytes))
+      Blocks& held = held_[dev];
+      int best = -1;
+      for (int i = 0; i < held.n; ++i)
+        if (held.b[i].bytes >= need && held.b[i].bytes <= 2 * need && (best < 0 || held.b[i].bytes < held.b[best].bytes))
           best = i;
-      if (best < held.size()) {
-        p = held[best].p;
-        *bytes = held[best].bytes;
-        held.erase(held.begin() + (ptrdiff_t)best);
+      if (best >= 0) {
+        p = held.b[best].p;
+        *bytes = held.b[best].bytes;
+        std::copy(held.b + best + 1, held.b + held.n, held.b + best);
+        --held.n;
       }
-      expired(dev, old);
+      held.move_first(held.unused(), old);
     }
-    to_driver(old);
+    old.to_driver();
     return p;
   }
   // Keeps p for later; false when it does not. idle: the caller has waited for all work that uses it.
@@ -1028,32 +1029,31 @@ class BlockStore {
       (void)hipGetLastError();
       return false;
     }
-    std::vector<Block> old;
+    Blocks old;
     {
       std::lock_guard<std::mutex> lock(mu_);
-      expired(dev, old);
-      std::vector<Block>& held = held_[dev];   // in the order of their coming
+      Blocks& held = held_[dev];
       size_t sum = bytes;
-      for (const Block& b : held) sum += b.bytes;
-      size_t drop = 0;
-      for (; sum > kMostHeld; ++drop) sum -= held[drop].bytes;
-      old.insert(old.end(), held.begin(), held.begin() + (ptrdiff_t)drop);
-      held.erase(held.begin(), held.begin() + (ptrdiff_t)drop);
-      held.push_back(Block{p, bytes, Clock::now()});
+      for (int i = 0; i < held.n; ++i) sum += held.b[i].bytes;
+      int drop = held.unused();
+      for (int i = 0; i < drop; ++i) sum -= held.b[i].bytes;
+      for (; sum > kMostHeld || held.n - drop == kMostBlocks; ++drop) sum -= held.b[drop].bytes;
+      held.move_first(drop, old);
+      held.b[held.n++] = Block{p, bytes, Clock::now()};
     }
-    to_driver(old);
+    old.to_driver();
     return true;
   }
   // Everything held of device dev back to the driver; whether there was anything.
   bool trim(int dev) {
     if (dev < 0 || dev >= kDevices) return false;
-    std::vector<Block> old;
+    Blocks old;
     {
       std::lock_guard<std::mutex> lock(mu_);
-      old.swap(held_[dev]);
+      held_[dev].move_first(held_[dev].n, old);
     }
-    to_driver(old);
-    return !old.empty();
+    old.to_driver();
+    return old.n > 0;
   }
 
  private:
@@ -1064,19 +1064,27 @@ class BlockStore {
     size_t bytes;
     Clock::time_point since;
   };
-  void expired(int dev, std::vector<Block>& out) {
-    std::vector<Block>& held = held_[dev];
-    const Clock::time_point now = Clock::now();
-    size_t n = 0;
-    while (n < held.size() && now - held[n].since > kKeep) ++n;
-    out.insert(out.end(), held.begin(), held.begin() + (ptrdiff_t)n);
-    held.erase(held.begin(), held.begin() + (ptrdiff_t)n);
-  }
-  static void to_driver(const std::vector<Block>& blocks) {
-    for (const Block& b : blocks) (void)hipFree(b.p);
-  }
+  struct Blocks {   // in the order of their coming
+    int n = 0;
+    Block b[kMostBlocks];
+    int unused() const {   // how many of the first ones are past kKeep
+      const Clock::time_point now = Clock::now();
+      int k = 0;
+      while (k < n && now - b[k].since > kKeep) ++k;
+      return k;
+    }
+    void move_first(int k, Blocks& to) {   // (to is empty)
+      std::copy(b, b + k, to.b);
+      to.n = k;
+      std::copy(b + k, b + n, b);
+      n -= k;
+    }
+    void to_driver() const {
+      for (int i = 0; i < n; ++i) (void)hipFree(b[i].p);
+    }
+  };
   std::mutex mu_;
-  std::vector<Block> held_[kDevices];
+  Blocks held_[kDevices];
 };
 BlockStore& block_store() {
   static BlockStore* store = new BlockStore();   // never destroyed: buffers may outlive the library's statics
@@ -1096,15 +1104,7 @@ struct DevBuf {
     size_t sz = need < 256 ? 256 : need;
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
     p = block_store().take(dev, sz, &sz);
-    if (!p) {
-      hipError_t e = hipMalloc(&p, sz);
-      if (e != hipSuccess && block_store().trim(dev)) e = hipMalloc(&p, sz);
-      if (e != hipSuccess) {
-        p = nullptr;
-        (void)hipGetLastError();   // reported here, not by the caller's next launch
-        return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", sz);
-      }
-    }
+    if (!p) CARVE_TRY(carve_device_alloc(&p, sz));
     bytes = sz;
     return CARVE_OK;
   }
@@ -1131,17 +1131,18 @@ struct PartSize {
   size_t need;
 };
 int carve_up(DevBuf& whole, std::initializer_list<PartSize> parts) {
-  std::vector<size_t> sizes;
-  size_t all = 0;
+  constexpr size_t kMostParts = 8;
+  size_t sizes[kMostParts], all = 0, k = 0;
+  if (parts.size() > kMostParts) return fail(CARVE_EINVAL, "carve_up: too many parts");
   for (const PartSize& q : parts) {
     const size_t n = std::max<size_t>({q.need, q.buf->bytes, 256});   // none shrinks
-    sizes.push_back(n);
+    sizes[k++] = n;
     all += (n + 255) / 256 * 256;
   }
   for (const PartSize& q : parts) q.buf->release();   // (so that none points into freed memory where there is not enough)
   CARVE_TRY(whole.reserve(all));
   uint8_t* at = whole.as<uint8_t>();
-  const size_t* n = sizes.data();
+  const size_t* n = sizes;
   for (const PartSize& q : parts) {
     q.buf->p = at;
     q.buf->bytes = *n;
@@ -1900,6 +1901,17 @@ extern "C" const char* carve_last_error(void) { return g_err.c_str(); }
 
 CARVE_HIDDEN int carve_fail_msg(int code, const char* msg) {
   return fail(code, "%s", msg);
+}
+
+CARVE_HIDDEN int carve_device_alloc(void** p, size_t bytes) {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && block_store().trim(dev)) e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return CARVE_OK;
+  *p = nullptr;
+  (void)hipGetLastError();   // reported here, not by the caller's next launch
+  return fail(CARVE_ENOMEM, "hipMalloc(%zu) failed", bytes);
 }
 
 extern "C" int sector_signatures_kind(uint32_t sig_kind, const void* sectors, uint64_t n_sectors, uint64_t* sigs,

@@ -114,7 +114,7 @@ extern "C" int ingest_create(const carve_index* idx, const carve_ingest_params* 
   bool ok = hipStreamCreateWithFlags(&in->copy, hipStreamNonBlocking) == hipSuccess &&
             hipStreamCreateWithFlags(&in->comp, hipStreamNonBlocking) == hipSuccess;   // default priority
   for (int b = 0; ok && b < 2; ++b)
-    ok = hipMalloc(&in->g[b], p.chunk_bytes) == hipSuccess &&
+    ok = carve_device_alloc((void**)&in->g[b], p.chunk_bytes) == CARVE_OK &&
          hipHostMalloc(&in->h[b], p.chunk_bytes, hipHostMallocDefault) == hipSuccess &&
          hipEventCreateWithFlags(&in->copied[b], hipEventDisableTiming) == hipSuccess &&
          hipEventCreateWithFlags(&in->done[b], hipEventDisableTiming) == hipSuccess;

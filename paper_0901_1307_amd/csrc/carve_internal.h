@@ -1,6 +1,7 @@
 // Library-internal entry points shared by carve.hip and carve_server.hip
 // (hidden: not part of the C ABI).
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/carve.h"
@@ -9,6 +10,10 @@
 
 // Records a message for carve_last_error() and returns `code`.
 CARVE_HIDDEN int carve_fail_msg(int code, const char* msg);
+
+// hipMalloc on the current device; when memory is short, again after the blocks
+// that the library keeps for later have gone back to the driver.
+CARVE_HIDDEN int carve_device_alloc(void** p, size_t bytes);
 
 // Bytes per master unit of an index: 512 (sectors) or 64 (fragments).
 CARVE_HIDDEN uint32_t carve_index_unit_bytes(const carve_index* idx);

@@ -226,7 +226,8 @@ int stage_host_jobs(carve_server* s, Lane& ln) {
     if (ln.arena) (void)hipFree(ln.arena);
     ln.arena = nullptr;
     ln.arena_cap = 0;
-    if (hipMalloc(&ln.arena, cap) != hipSuccess) return carve_fail_msg(CARVE_ENOMEM, "server: arena allocation failed");
+    if (carve_device_alloc(&ln.arena, cap) != CARVE_OK)
+      return carve_fail_msg(CARVE_ENOMEM, "server: arena allocation failed");
     ln.arena_cap = cap;
   }
   uint64_t at = 0;

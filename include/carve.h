@@ -260,7 +260,10 @@ int scan_counts(carve_scan* sc, uint64_t* n_flagged, uint64_t* n_confirmed);
  * run beside them. Nothing to wait for before the first scan. An ordering
  * point only: no results are handed over (the scan's outputs are read after
  * its compaction, on its own stream), so the wait carries no system-scope
- * cache fence. For keeping several steps in flight on several streams
+ * cache fence. An object that has been scanned 16 times without this call stops
+ * marking where its kernels end: the next call then waits for everything enqueued
+ * on the scan's stream so far, and from there on its scans mark it again. For
+ * keeping several steps in flight on several streams
  * (Section 3.2's pipeline of scans, with the host never waiting between
  * them).
  * Errors: EINVAL (null sc), EDEVICE.

@@ -44,3 +44,27 @@ def test_first_scan_of_an_object(kind):
     assert not end.query()                   # what came behind the scan is still running
     torch.cuda.synchronize()
     assert carve.scan_counts(sc)[0] > 0
+
+
+def test_first_wait_after_many_scans():
+    """An object scanned many times without a wait: its first wait is for all that its stream holds,
+    the next ones are for the kernel alone again."""
+    data = torch.randint(0, 256, (64 * SECTOR,), dtype=torch.uint8, device="cuda")
+    image = torch.cat([data] * 128)
+    idx = carve.build_master_index(data, [0, 64])
+    ours, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(ours):
+        sc = carve.scan_image(idx, image)
+        for n in range(2, 20):
+            carve.scan_image(idx, image, scan=sc)
+        for alone in (False, True, True):
+            carve.scan_image(idx, image, scan=sc)
+            torch.cuda._sleep(100_000_000)
+            end = torch.cuda.Event()
+            end.record()
+            carve.scan_wait_kernel(sc, other)
+            other.synchronize()
+            assert end.query() != alone
+            torch.cuda.synchronize()
+    assert carve.scan_counts(sc)[0] == 128 * 64

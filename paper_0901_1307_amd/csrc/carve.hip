@@ -1023,15 +1023,9 @@ class BlockStore {
     old.to_driver();
     return p;
   }
-  // Keeps p for later; false when it does not. idle: the caller has waited for all work that uses it.
-  bool give(int dev, void* p, size_t bytes, bool idle) {
-    int cur = -1;
-    if (bytes < kLeast || bytes > kMostHeld || dev < 0 || dev >= kDevices || hipGetDevice(&cur) != hipSuccess || cur != dev)
-      return false;
-    if (!idle && hipDeviceSynchronize() != hipSuccess) {   // (as while a stream is being captured)
-      (void)hipGetLastError();
-      return false;
-    }
+  // Keeps p, which no work uses any more, for later; false when it does not.
+  bool give(int dev, void* p, size_t bytes) {
+    if (bytes < kLeast || bytes > kMostHeld || dev < 0 || dev >= kDevices) return false;
     Blocks old;
     {
       std::lock_guard<std::mutex> lock(mu_);
@@ -1094,6 +1088,19 @@ BlockStore& block_store() {
   return *store;
 }
 
+// Waits until the work of device dev so far has ended, with what a free does:
+// freeing any block waits for that, and unlike hipDeviceSynchronize it may be
+// called while some stream is being captured in relaxed mode. False when it failed
+// or dev is not the current device.
+bool device_idle(int dev) {
+  void* p = nullptr;
+  int cur = -1;
+  if (hipGetDevice(&cur) == hipSuccess && cur != dev) return false;
+  if (hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Device buffer that grows on demand (contents not preserved), or a part of
 // another one (carve_up).
 struct DevBuf {
@@ -1113,9 +1120,9 @@ struct DevBuf {
   }
   template <class T>
   T* as() const { return (T*)p; }
-  // idle: the caller has waited for all work that uses it
+  // idle: the caller has waited for all work that uses it, so it may be kept for another buffer
   void release(bool idle = false) {
-    if (p && !part && !block_store().give(dev, p, bytes, idle)) (void)hipFree(p);
+    if (p && !part && !(idle && block_store().give(dev, p, bytes))) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
     part = false;
@@ -1449,8 +1456,8 @@ struct carve_index {
 // What a confirmation keeps per flagged unit and its records.
 struct ConfirmBufs {
   DevBuf mem, n_match, match_mask, range_sums, matches;   // the others are parts of mem
-  void release() {
-    for (DevBuf* b : {&n_match, &match_mask, &range_sums, &matches, &mem}) b->release();
+  void release(bool idle) {
+    for (DevBuf* b : {&n_match, &match_mask, &range_sums, &matches, &mem}) b->release(idle);
   }
 };
 // An enqueued confirmation, and where its records go: bufs->matches (rec_cap of
@@ -1955,8 +1962,9 @@ extern "C" void free_index(carve_index* idx) {
   idx->sorted_slot.release();
   idx->lds_filter.release();
   idx->bloom_tau.release();
-  idx->mem.release();
-  idx->filters.release();
+  const bool idle = device_idle(idx->device);
+  idx->mem.release(idle);
+  idx->filters.release(idle);
   delete idx;
 }
 
@@ -2299,10 +2307,11 @@ extern "C" int index_get_scan_config(const carve_index* idx, carve_scan_config* 
 extern "C" void free_scan(carve_scan* sc) {
   if (!sc) return;
   (void)hipStreamSynchronize(sc->stream);
+  const bool idle = device_idle(sc->device);
   for (DevBuf* b : {&sc->d_desc, &sc->bitmap, &sc->ids, &sc->img_of, &sc->count, &sc->hit_slot, &sc->img_off,
                     &sc->tau_words, &sc->ws, &sc->scan_mem, &sc->again})
-    b->release();
-  for (auto& b : sc->conf) b->release();
+    b->release(idle);
+  for (auto& b : sc->conf) b->release(idle);
   sc->h_desc.release();
   sc->h_count.release();
   sc->h_img_off.release();

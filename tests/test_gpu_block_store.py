@@ -69,6 +69,31 @@ def test_indexes_one_after_another_on_threads(layout):
         raise errors[0]
 
 
+def test_objects_freed_while_a_stream_is_captured():
+    """Freeing indexes and scan objects does not end a capture that allows frees beside it."""
+    masters = torch.randint(0, 256, (100_000 * SECTOR,), dtype=torch.uint8, device="cuda")
+    image = masters[:20_000 * SECTOR].clone()
+    idx, other = (carve.build_master_index(masters, [0, 100_000]) for _ in range(2))
+    sc, gone = carve.scan_image(idx, image), carve.scan_image(other, image)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        carve.scan_image(idx, image, scan=sc)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream, capture_error_mode="relaxed"):
+            carve.scan_image(idx, image, scan=sc)
+            gone.close()
+            other.close()
+    for left in (20_000, 12_345):
+        image[left * SECTOR:] = 0
+        third = carve.build_master_index(masters[:60_000 * SECTOR], [0, 60_000])   # takes what was freed
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert carve.scan_counts(sc)[0] == left
+        third.close()
+
+
 def test_bounded_given_back_when_wanted_and_when_unused():
     image = torch.zeros(5 << 30, dtype=torch.uint8, device="cuda")   # 120 MiB of ids and slots
     before = _free()

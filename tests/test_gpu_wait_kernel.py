@@ -68,3 +68,30 @@ def test_first_wait_after_many_scans():
             assert end.query() != alone
             torch.cuda.synchronize()
     assert carve.scan_counts(sc)[0] == 128 * 64
+
+
+def test_two_streams_in_one_capture():
+    """Objects made during a capture, the second one's stream joined by scan_wait_kernel."""
+    data = torch.randint(0, 256, (64 * SECTOR,), dtype=torch.uint8, device="cuda")
+    image = torch.cat([data] * 16)
+    idx = carve.build_master_index(data, [0, 64])
+    ours, other = torch.cuda.Stream(), torch.cuda.Stream()
+    first, second = carve.Scan(), carve.Scan()
+    with torch.cuda.stream(ours):
+        carve.scan_image(idx, image)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=ours, capture_error_mode="relaxed"):
+            carve.scan_image(idx, image, scan=first)
+            carve.scan_wait_kernel(first, other)
+            with torch.cuda.stream(other):
+                carve.scan_image(idx, image, tau_mode=carve.CARVE_TAU_ANY, scan=second)
+                carve.confirm_enqueue(idx, second)
+            ours.wait_stream(other)
+            carve.confirm_enqueue(idx, first)
+    for gone in range(3):
+        image[gone * SECTOR:(gone + 1) * SECTOR] = 0
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert carve.scan_counts(first) == carve.scan_counts(second) == (16 * 64 - gone - 1, 16 * 64 - gone - 1)

@@ -1308,7 +1308,18 @@ bool scan_without_loop(uint32_t per_cu_cap, uint32_t chunk, uint64_t n_tiles) {
 template <int kMode, int kSig, int kLayout, class Src>
 void launch_k_scan_as(const Src& src, uint64_t n_tiles, uint32_t chunk, uint32_t per_cu_cap, const IndexView& ix,
                       uint64_t* out, uint32_t* hit_slot, const ScanQueue& q) {
-  if (scan_without_loop(per_cu_cap, chunk, n_tiles)) {
+  bool without_loop = scan_without_loop(per_cu_cap, chunk, n_tiles);
+  // A sorted index without a filter is searched for every sector, and the four
+  // lanes that a wave of 16 sectors has for each make the search four times over:
+  // past 64 MiB the persistent kernel, at its best 2 blocks a CU (1M masters, 64 MiB
+  // 24.3 / 23.6 us, 256 MiB 88.4 / 75.5, 2 GiB 697 / 546; 16 MiB 8.5 / 10.0).
+  constexpr uint64_t kSearchedTiles = 2048;
+  if constexpr (kMode != kSigs && kSig == kSigDjb2 && kLayout == kLayoutSorted)
+    if (without_loop && !ix.bloom && n_tiles > kSearchedTiles) {
+      without_loop = false;
+      per_cu_cap = 2;
+    }
+  if (without_loop) {
     if constexpr (kSig == kSigDjb2)
       launch_marked(q, k_scan_parts<kMode, Src, kLayout>, n_tiles * kTileParts, kWave, src, ix, out, hit_slot);
     else

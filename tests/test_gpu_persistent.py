@@ -44,3 +44,31 @@ def test_runs_of_tiles(shape, bloom, kind):
         rec = carve.batch_confirm_matches(idx, b)
         rec["disk_sector"] += np.array(cuts, dtype=np.uint64)[rec["image"]]
         assert_same_matches(rec[list(want.dtype.names)], want)
+
+
+@pytest.mark.parametrize("words", [2048, 2049])
+def test_sorted_without_filter(words):
+    """Both sides of the line from which a sorted index without a filter is scanned by the persistent
+    kernel, against the bucketed index's results."""
+    g = torch.Generator(device="cuda").manual_seed(words)
+    masters = torch.randint(-2**62, 2**62, (5000 * 64,), device="cuda", generator=g).view(torch.uint8).view(-1, SECTOR)
+    n = 64 * words - 13
+    image = torch.randint(-2**62, 2**62, (n * 64,), device="cuda", generator=g).view(torch.uint8).view(-1, SECTOR)
+    at = torch.cat([torch.arange(0, n, 101, device="cuda"), torch.arange(n - 70, n, device="cuda")])
+    image[at] = masters[torch.randint(5000, (at.numel(),), device="cuda", generator=g)]
+    dev = image.view(-1)
+    plain = carve.build_master_index(masters.view(-1), [0, 2000, 5000])
+    idx = carve.build_master_index(masters.view(-1), [0, 2000, 5000], layout=2, bloom_bits_per_key=carve.CARVE_BLOOM_OFF)
+    for tau0, any_tau in ((5, False), (0, True)):
+        want_flags, want, _ = gpu_flags_and_matches(plain, dev, tau0, any_tau)
+        assert len(want) > 100
+        flags, matches, _ = gpu_flags_and_matches(idx, dev, tau0, any_tau)
+        assert np.array_equal(flags, want_flags)
+        assert_same_matches(matches, want)
+        ids = torch.full((n,), -1, dtype=torch.int64, device="cuda")
+        count = torch.zeros(1, dtype=torch.int64, device="cuda")
+        carve.scan_image_noalloc(idx, dev, ids, count, tau0, int(any_tau))
+        assert np.array_equal(ids[:int(count)].cpu().numpy().astype(np.uint64), want_flags)
+        b = carve.scan_batch(idx, [(dev[:4096 * SECTOR], tau0, int(any_tau)), (dev[4096 * SECTOR:], tau0, int(any_tau))])
+        got = torch.cat([carve.batch_flagged_sectors(b, 0), carve.batch_flagged_sectors(b, 1) + 4096])
+        assert np.array_equal(got.numpy().astype(np.uint64), want_flags)

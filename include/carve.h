@@ -251,6 +251,9 @@ int flagged_sectors_enqueue(carve_scan* sc, uint64_t* out, uint64_t cap);
  * readback: the flagged units of the latest scan (a batch: of all its images)
  * and the records of a confirmation that ran after it, or
  * CARVE_NOT_CONFIRMED when none did.
+ * (A window scan with more flagged windows than its enqueued confirmation has
+ * room for, see scan_fragments: the records of the windows that had room.
+ * confirm_matches confirms all of them.)
  * Errors: EINVAL (null argument), EDEVICE.
  */
 int scan_counts(carve_scan* sc, uint64_t* n_flagged, uint64_t* n_confirmed);

@@ -1090,15 +1090,16 @@ BlockStore& block_store() {
 
 // Waits until the work of device dev so far has ended, with what a free does:
 // freeing any block waits for that, and unlike hipDeviceSynchronize it may be
-// called while some stream is being captured in relaxed mode. False when it failed
-// or dev is not the current device.
-bool device_idle(int dev) {
+// called while some stream is being captured in relaxed mode. Returns dev, or
+// kNoDevice when it failed or dev is not the current device.
+constexpr int kNoDevice = -1;
+int device_idle(int dev) {
   void* p = nullptr;
-  int cur = -1;
-  if (hipGetDevice(&cur) == hipSuccess && cur != dev) return false;
-  if (hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess) return true;
+  int cur = kNoDevice;
+  if (hipGetDevice(&cur) == hipSuccess && cur != dev) return kNoDevice;
+  if (hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess) return dev;
   (void)hipGetLastError();
-  return false;
+  return kNoDevice;
 }
 
 // Device buffer that grows on demand (contents not preserved), or a part of
@@ -1107,12 +1108,12 @@ struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   bool part = false;
-  int dev = -1;
+  int dev = kNoDevice;
   int reserve(size_t need) {
     if (need <= bytes) return CARVE_OK;
     release();
     size_t sz = need < 256 ? 256 : need;
-    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) dev = kNoDevice;
     p = block_store().take(dev, sz, &sz);
     if (!p) CARVE_TRY(carve_device_alloc(&p, sz));
     bytes = sz;
@@ -1120,9 +1121,10 @@ struct DevBuf {
   }
   template <class T>
   T* as() const { return (T*)p; }
-  // idle: the caller has waited for all work that uses it, so it may be kept for another buffer
-  void release(bool idle = false) {
-    if (p && !part && !(idle && block_store().give(dev, p, bytes))) (void)hipFree(p);
+  // idle: the device on which the caller has waited for all work that uses it; the block may then be kept for
+  // another buffer
+  void release(int idle = kNoDevice) {
+    if (p && !part && !(idle == dev && block_store().give(dev, p, bytes))) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
     part = false;
@@ -1467,7 +1469,7 @@ struct carve_index {
 // What a confirmation keeps per flagged unit and its records.
 struct ConfirmBufs {
   DevBuf mem, n_match, match_mask, range_sums, matches;   // the others are parts of mem
-  void release(bool idle) {
+  void release(int idle) {
     for (DevBuf* b : {&n_match, &match_mask, &range_sums, &matches, &mem}) b->release(idle);
   }
 };
@@ -1973,7 +1975,7 @@ extern "C" void free_index(carve_index* idx) {
   idx->sorted_slot.release();
   idx->lds_filter.release();
   idx->bloom_tau.release();
-  const bool idle = device_idle(idx->device);
+  const int idle = device_idle(idx->device);
   idx->mem.release(idle);
   idx->filters.release(idle);
   delete idx;
@@ -2281,7 +2283,7 @@ int build_index(const void* master_sectors, const uint64_t* file_sector_offsets,
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
       return bail2(fail(CARVE_EDEVICE, "build_fragment_index: filter build failed"));
   }
-  work.release(true);   // (the stream was waited for after its last use)
+  work.release(ix->device);   // (the stream was waited for after its last use)
   *out = ix;
   return CARVE_OK;
 }
@@ -2318,7 +2320,7 @@ extern "C" int index_get_scan_config(const carve_index* idx, carve_scan_config* 
 extern "C" void free_scan(carve_scan* sc) {
   if (!sc) return;
   (void)hipStreamSynchronize(sc->stream);
-  const bool idle = device_idle(sc->device);
+  const int idle = device_idle(sc->device);
   for (DevBuf* b : {&sc->d_desc, &sc->bitmap, &sc->ids, &sc->img_of, &sc->count, &sc->hit_slot, &sc->img_off,
                     &sc->tau_words, &sc->ws, &sc->scan_mem, &sc->again})
     b->release(idle);

@@ -987,9 +987,8 @@ int fail(int code, const char* fmt, ...) {
 // Device blocks that the library's buffers gave up, kept for its next ones. What
 // a block costs when it comes from the driver and goes back to it differs from
 // machine to machine and from one call to the next (some MiB: mostly 10 us, now
-// and then 300, 570 for a free of 64 MiB; elsewhere most of a millisecond), and
-// an index build and the first scan with it take five and give them back when
-// they are done.
+// and then 300, 570 for a free of 64 MiB), and an index build and the first scan
+// with it take five and give them back when they are done.
 // It holds memory, never contents. A block enters it once all work enqueued on
 // its device has ended (what freeing it waits for as well), so whoever gets it
 // may use it on any stream. Bounded: kMostHeld bytes per device, 0.2% of it, the

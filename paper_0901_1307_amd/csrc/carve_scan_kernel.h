@@ -217,9 +217,11 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 // 60 registers eight waves fit a SIMD, 64 KiB of loads in flight on each, and
 // the hardware hands out the next block as a wave ends, so nothing is idle
 // before the last few microseconds. Against the persistent grid of tiles of 64
-// sectors (k_scan, with the same hashing): 1 MiB 6.2 -> 5.1 us, 64 MiB 16.3 ->
-// 13.2, 700 MiB 122 -> 110, 8 GiB 1308 -> 1257 (1253 at that grid's best
-// shape), 6.8 TB/s and bound by HBM. Blocks of four waves were 0-2% slower, 32
+// sectors (k_scan, with the same hashing, 2 blocks a CU), two passes of one run:
+// 16 MiB 6.6, 7.4 -> 4.7, 4.6 us; 64 MiB 14.3, 14.9 -> 11.9, 12.6; 700 MiB 113,
+// 117 -> 105, 109; 8 GiB 1255, 1262 -> 1214, 1253, 6.9-7.1 TB/s and bound by HBM
+// (that grid at 1 block a CU, its best there: 1241, 1245, so 2% slower and 1%
+// faster). When they were tried, blocks of four waves were 0-2% slower, 32
 // sectors a wave 1% faster on 8 GiB and up to 7% slower below 1 GiB.
 constexpr uint32_t kPart = 16;                          // sectors per wave
 constexpr uint32_t kTileParts = kTileSectors / kPart;
@@ -252,8 +254,10 @@ __device__ __forceinline__ uint32_t part_valid(uint64_t n, uint64_t first) {
 // The CRC's counterpart: a wave per tile of 64 sectors, since the CRC is a chain
 // over a sector's bytes that one lane runs; four waves to a block (their staging
 // areas are what bounds the waves of a CU, at 16). Against the persistent grid at
-// its best shape (2 blocks per CU): 1 MiB 7.9 -> 7.1 us, 700 MiB 120 -> 115, 2 GB
-// 330 -> 313, 8 GiB 1307 -> 1249; one wave to a block: 7.0, 117, 318, 1268.
+// 2 blocks a CU, two passes: 64 MiB 14.6, 14.5 -> 13.2, 13.4 us; 700 MiB 116, 116
+// -> 110, 110; 2 GiB 322, 322 -> 305, 305; 8 GiB 1268, 1271 -> 1195, 1197. When it
+// was tried, one wave to a block took 7.0 against 7.1 us on 1 MiB and 1.5% more
+// from 700 MiB on.
 template <int kMode, class Src, int kLayout>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_scan_tiles(
     Src src, uint64_t n_tiles, IndexView ix, uint64_t* __restrict__ out, uint32_t* __restrict__ hit_slot) {
@@ -453,10 +457,12 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
 
 // The same split for k_scan_parts' way of scanning: block b takes, of position
 // p = b mod 8 (so on XCD p), part (b / 8) mod 4 of tile b / 32. The hardware's
-// hand-out of blocks balances each XCD's waves, so there are no claims: 2651 us
-// against 2722 (2630 at its best launch shape) for k_scan_tau on 16 GiB and 16 M
-// masters, 171 against 199 on 1 GiB. Every word of tau_words is written, the
-// tiles past a position's sectors with zeros.
+// hand-out of blocks balances each XCD's waves, so there are no claims. 16 M
+// masters, against k_scan_tau at 2 blocks a CU (and at 1): 64 MiB 13 us against 40
+// (29), 1 GiB 164 against 193 (178), 4 GiB 650 against 678 (647), 16 GiB 2583
+// against 2649 (2540): k_scan_tau at 1 block a CU is up to 2% faster on large
+// images, and 9% slower at 1 GiB. Every word of tau_words is written, the tiles
+// past a position's sectors with zeros.
 template <int kLayout, bool kSlots>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void k_scan_tau_parts(
     const uint8_t* __restrict__ image, uint64_t n_sectors, uint32_t tau0, uint64_t words_per_pos, IndexView ix,
